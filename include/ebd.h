@@ -193,10 +193,11 @@ typedef struct ebd_attend_params {
  *   be 16-byte aligned.  After the call the workspace starts with two uint32 counts per (unit,
  *   block of 8 query heads): the 512-row chunks re-read to make the range term exact (0 when
  *   the kept candidates already decide it), then the heads whose vhat was summed directly.
- *   Then, when units span several splits, one partial record per (unit, split, query head).
- *   A unit of up to 4 splits runs them as the waves of one work-group, the last of which
- *   finalizes it, so the step is one kernel; units of more splits take a second kernel that
- *   combines the records.  When every unit fits one split the workspace holds only the counts.
+ *   Then, when units span several splits, room for one partial record per (unit, split, query
+ *   head).  A unit of up to 8 splits runs them as the waves of one work-group that also finalizes
+ *   it, so the step is one kernel; with split_rows = 0 the library may deal a unit's rows over
+ *   other waves and fewer records than the size was planned for.  Units of several records take
+ *   a second kernel that combines them.
  */
 ebd_status ebd_attend_certify(const ebd_attend_params *p, const uint16_t *q, const uint16_t *Kc,
                               const uint16_t *Vc, const float *pic, const int32_t *count,

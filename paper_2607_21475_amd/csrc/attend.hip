@@ -26,12 +26,12 @@
 //   g^2 |v|^2 (g^2 = (1 - pi) w^2) plus the maxima of g |v| and of g over what it dropped, so
 //   a chunk holds 32 candidates per head with bounds for the rest.
 //   The running max m moves lazily (only by jumps of more than 2^8 in weight).
-//   A unit cut into 2..4 splits (when their LDS fits one work-group) runs them as the waves
-//   of one work-group instead of as separate work-groups.
-// Finalize (yhat, Vhat, ln Nhat, the exact range term b and the radius r): a unit that is one
-//   split is finalized by the same wave from LDS; a unit whose splits share a work-group by the
-//   wave that arrives last (an LDS counter, work-group fences); any other unit cut into splits
-//   by attend_finalize (one wave per (unit, head block)).  The split records are combined by
+//   With fewer units than keep the chip busy, up to eight waves of one work-group share a unit's
+//   rows, and long units of small launches are cut further into parts (a work-group each).
+// Finalize (yhat, Vhat, ln Nhat, the exact range term b and the radius r): a unit that one wave
+//   read whole is finalized by it from LDS, all heads together; a unit that a work-group shares by
+//   its waves, a head each, from their sums in LDS; a unit cut into records by attend_finalize (one
+//   wave per (unit, head)).  The waves' and records' sums are combined by
 //   log-sum-exp.  Candidates are bounded a chunk block at a time; only those whose bound can
 //   still win are re-read, and a chunk is rescanned only if its non-candidate bound cannot
 //   exclude a larger term.  Where C2 - 2 yhat.Cv + |yhat|^2 C0 has cancelled (one tail row
@@ -119,7 +119,7 @@ constexpr int kPivLogit = 25;
 template <bool PL_LDS>
 __device__ __forceinline__ void split_tile(SplitState &S, const Tile &T, const bf16x8 (&qop)[4],
                                            int nvalid, int rowbase, bool isC, bool plain,
-                                           float scale2, float *s_piv, int hslot, bool isW) {
+                                           float scale2, float *piv, bool isW) {
   f32x4 sacc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb)
@@ -139,7 +139,7 @@ __device__ __forceinline__ void split_tile(SplitState &S, const Tile &T, const b
 #pragma unroll
   for (int i = 0; i < 4; ++i) lg[i] = i < nvalid ? fmaf(sacc[i], scale2, -lp[i]) : -INFINITY;
   float lmax = fmaxf(fmaxf(lg[0], lg[1]), fmaxf(lg[2], lg[3]));
-  const float pl = PL_LDS ? s_piv[hslot * kPivFloats + kPivLogit] : S.pl;
+  const float pl = PL_LDS ? piv[kPivLogit] : S.pl;
   if (__any(lmax > pl + kPivGap)) {
     // a new pivot for some head: the tile's largest logit of each column and its row (the lowest
     // of equal ones); both columns of a head see the same logits and decide alike
@@ -152,10 +152,10 @@ __device__ __forceinline__ void split_tile(SplitState &S, const Tile &T, const b
     r = min(r, __shfl_xor(r, 16));
     r = min(r, __shfl_xor(r, 32));
     const int rr = r & 15;
-    const int pn = __float_as_int(s_piv[hslot * kPivFloats]);  // the list's count
+    const int pn = __float_as_int(piv[0]);  // the list's count
     if (tm > pl + kPivGap && pn < kPivMax) {
       if (isW && g == (rr >> 2)) {  // the weight lane holding the row records it
-        float *e = s_piv + hslot * kPivFloats;
+        float *e = piv;
         const float pa = (rr & 1) ? T.p[1] : T.p[0], pb = (rr & 1) ? T.p[3] : T.p[2];
         e[1 + 3 * pn] = __int_as_float(rowbase - 4 * g + rr);
         e[2 + 3 * pn] = tm;
@@ -285,10 +285,10 @@ __device__ __forceinline__ void split_tile(SplitState &S, const Tile &T, const b
 // End of a chunk: the lane lists of head h (weight lanes (g, h), variance lanes (g, GB + h))
 // become the chunk's 32 candidates in LDS, with the chunk's dropped maxima and the running max
 // they are scaled by; the lists restart empty for the next chunk.  `c0` is the chunk's first
-// unit row.
+// unit row; head h's blocks start at s_chunk + h hstride.
 template <int GB>
-__device__ __forceinline__ void flush_chunk(SplitState &S, float *s_chunk, int k, int g, int c,
-                                            int c0) {
+__device__ __forceinline__ void flush_chunk(SplitState &S, float *s_chunk, int hstride, int k, int g,
+                                            int c, int c0) {
   float dk = S.dk, dg = S.dg, vm = 0.0f;
 #pragma unroll
   for (int e = 0; e < 4; ++e) vm = fmaxf(vm, S.cg[e] > 0.0f ? S.ck[e] / S.cg[e] : 0.0f);
@@ -308,7 +308,7 @@ __device__ __forceinline__ void flush_chunk(SplitState &S, float *s_chunk, int k
   if (c < 2 * GB) {
     const int h = c < GB ? c : c - GB;
     const int j0 = (c < GB ? 0 : 16) + 4 * g;
-    float *blk = s_chunk + (k * GB + h) * kChunkFloats;
+    float *blk = s_chunk + h * hstride + k * kChunkFloats;
     uint32_t off[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -341,7 +341,7 @@ __device__ __forceinline__ void flush_chunk(SplitState &S, float *s_chunk, int k
 // Finalize of a block of GB heads of one unit: yhat, Vhat, ln Nhat, the exact range term b and
 // the radius r, from the combined sums in LDS and the candidate blocks of every chunk.
 // ---------------------------------------------------------------------------------------------
-constexpr int kListCap = 256;  // candidates evaluated per batch
+constexpr int kListCap = 240;  // candidates evaluated per batch
 // per-head table: M, l, C0, C2, |yhat|, lb, Vhat, redo, then the pivot: logit (-inf: none), pi,
 // row, key (split * kPivMax + entry)
 constexpr int kHs = 12;
@@ -365,9 +365,10 @@ struct FinLds {
   float *hs;                 // [GB][kHs]
   unsigned long long *best;  // [GB]: (bound bits << 32) | candidate index of the largest bound
   int *list;                 // [kListCap]
-  __device__ explicit FinLds(float *base) {
-    o = base;
-    hs = o + 2 * GB * kHeadDim;
+  __device__ explicit FinLds(float *base) : FinLds(base, base + 2 * GB * kHeadDim) {}
+  __device__ FinLds(float *sums, float *rest) {
+    o = sums;
+    hs = rest;
     best = reinterpret_cast<unsigned long long *>(hs + GB * kHs);
     list = reinterpret_cast<int *>(best + GB);
   }
@@ -377,15 +378,15 @@ struct FinLds {
   }
 };
 
-// Where the candidate block of (split s, chunk k, head h) lives: LDS for a fused split, the
-// split records in the workspace otherwise.
+// Where the candidate block (record s, block kk, head h) lives: LDS for a unit finalized where it
+// was read, the split records in the workspace otherwise.
 struct CandSrc {
   const float *base;
   int64_t sstride;
   int kstride, hstride;
 };
 
-// Where the pivot list of (split s, head h) lives: LDS for a fused split, the records otherwise.
+// Where the pivot list of (record s, head h) lives.
 struct PivSrc {
   const float *base;
   int64_t sstride;
@@ -393,54 +394,72 @@ struct PivSrc {
   __device__ const float *at(int s, int h) const { return base + s * sstride + h * hstride; }
 };
 
-// Calls f(row, logit, pi, key) for every pivot entry of head h over the splits, in a fixed order
-// (split, entry); key = split * kPivMax + entry.  All lanes of a head run the same iterations.
-template <class Fn>
-__device__ __forceinline__ void for_each_pivot(const PivSrc &P, int nsp, int h, bool act, Fn &&f) {
-  for (int s = 0; s < nsp; ++s) {
-    const float *pl = P.at(s, h);
-    const int n = act ? __float_as_int(pl[0]) : 0;
-#pragma unroll
-    for (int e = 0; e < kPivMax; ++e)
-      if (e < n) f(__float_as_int(pl[1 + 3 * e]), pl[2 + 3 * e], pl[3 + 3 * e], s * kPivMax + e);
+// Which rows a candidate block covers.  A record holds the blocks of W waves (nch each, wave w of
+// record s over unit rows (s W + w) r .. + r - 1), then nb - W nch blocks of pivot entries that were
+// added back to its sums (their row offsets count from the record's first row; nothing to rescan).
+struct BlockGeo {
+  int r, W, nch, nb;
+  // first row of block kk of record s, and the end of its rows (its first row if it has none)
+  __device__ __forceinline__ void rows(int s, int kk, int cnt, int &ra, int &rz) const {
+    const int w = kk / nch;
+    if (w >= W) {
+      ra = rz = s * W * r;
+      return;
+    }
+    const int w0 = (s * W + w) * r;
+    ra = w0 + (kk - w * nch) * kChunkRows;
+    rz = min(cnt, min(w0 + r, ra + kChunkRows));
   }
+  // whether the block was written (a block of added-back pivots is, with its record)
+  __device__ __forceinline__ bool present(int s, int kk, int cnt, int &ra) const {
+    int rz;
+    rows(s, kk, cnt, ra, rz);
+    return kk >= W * nch ? ra < cnt : ra < rz;
+  }
+};
+
+// Calls f(row, logit, pi, entry) for every pivot entry of head h's one list, in order.  All lanes of
+// a head run the same iterations.
+template <class Fn>
+__device__ __forceinline__ void for_each_pivot(const float *pl, bool act, Fn &&f) {
+  const int n = act ? __float_as_int(pl[0]) : 0;
+#pragma unroll
+  for (int e = 0; e < kPivMax; ++e)
+    if (e < n) f(__float_as_int(pl[1 + 3 * e]), pl[2 + 3 * e], pl[3 + 3 * e], e);
 }
 
-// Before the finalize: per head, the entry with the largest logit over all splits becomes the
-// pivot (kept in the head's table), the running max is raised to its logit if needed (the sums
-// rescaled), and every other entry is added back into l, o, C0, Cv, C2 exactly.  8 lanes per
-// head, 16 dims per lane.
+// Sixteen bf16 values (dims 16 j .. 16 j + 15) of retained row `row` of the unit.
+struct Row16 {
+  uint32_t w[8];
+  __device__ __forceinline__ void load(const uint16_t *Vc, int64_t cbase, int row, int j) {
+    const uint4 *vr = reinterpret_cast<const uint4 *>(Vc + (cbase + row) * kHeadDim + 16 * j);
+    const uint4 a = vr[0], b = vr[1];
+    w[0] = a.x, w[1] = a.y, w[2] = a.z, w[3] = a.w;
+    w[4] = b.x, w[5] = b.y, w[6] = b.z, w[7] = b.w;
+  }
+};
+
+// Before the finalize of a unit that one wave read whole: per head, the list entry with the largest
+// logit becomes the pivot (kept in the head's table), the running max is raised to its logit if
+// needed (the sums rescaled), and every other entry is added back into l, o, C0, Cv, C2 exactly.
+// 8 lanes per head, 16 dims per lane.
 template <int GB>
-__device__ __forceinline__ void pivot_prepare(const AttendLaunch &L, int64_t cbase, int nsp, const PivSrc &P,
-                              const FinLds<GB> &F) {
+__device__ __forceinline__ void pivot_prepare(const AttendLaunch &L, int64_t cbase, const PivSrc &P,
+                                              const FinLds<GB> &F) {
   const int lane = threadIdx.x & 63;
   const int h = lane >> 3, j = lane & 7;
   const bool act = h < GB;
   const int hh = act ? h : 0;
   wave_sync();  // the sums are in LDS
-  // the pivot: lanes of a head look at every eighth split, then compare
+  const float *plist = P.at(0, hh);
   float bl = -INFINITY;
   int bk = 0x7fffffff;
-  for (int s = j; s < nsp; s += 8) {
-    const float *pl = P.at(s, hh);
-    const int n = act ? __float_as_int(pl[0]) : 0;
-#pragma unroll
-    for (int e = 0; e < kPivMax; ++e) {
-      if (e < n && pl[2 + 3 * e] > bl) {
-        bl = pl[2 + 3 * e];
-        bk = s * kPivMax + e;
-      }
+  for_each_pivot(plist, act, [&](int, float lgt, float, int key) {
+    if (lgt > bl) {
+      bl = lgt;
+      bk = key;
     }
-  }
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) {
-    const float ol = __shfl_xor(bl, o);
-    const int ok = __shfl_xor(bk, o);
-    if (ol > bl || (ol == bl && ok < bk)) {
-      bl = ol;
-      bk = ok;
-    }
-  }
+  });
   float *hs = F.hs + hh * kHs;
   const float M0 = hs[kHsM], M1 = fmaxf(M0, bl);
   const float f = scale_of(M0, M1), f2 = f * f;
@@ -456,7 +475,7 @@ __device__ __forceinline__ void pivot_prepare(const AttendLaunch &L, int64_t cba
     }
   }
   float la = 0.0f, c0a = 0.0f, c2a = 0.0f;
-  for_each_pivot(P, nsp, hh, act, [&](int row, float lgt, float p, int key) {
+  for_each_pivot(plist, act, [&](int row, float lgt, float p, int key) {
     if (key == bk) return;
     const float w = fast_exp2(lgt - M1), cc = (1.0f - p) * w * w;
     const uint4 *vr = reinterpret_cast<const uint4 *>(L.Vc + (cbase + row) * kHeadDim + 16 * j);
@@ -497,7 +516,7 @@ __device__ __forceinline__ void pivot_prepare(const AttendLaunch &L, int64_t cba
       hs[kHsPl] = bl;
       hs[kHsPk] = __int_as_float(bk);
       if (bl > -INFINITY) {
-        const float *pe = P.at(bk / kPivMax, hh) + 1 + 3 * (bk % kPivMax);
+        const float *pe = plist + 1 + 3 * bk;
         hs[kHsPr] = pe[0];
         hs[kHsPp] = pe[2];
       }
@@ -506,9 +525,13 @@ __device__ __forceinline__ void pivot_prepare(const AttendLaunch &L, int64_t cba
   wave_sync();
 }
 
+// Outputs of heads h0 .. h0 + GB - 1 of a unit by one wave: yhat, Vhat, ln Nhat, b, r from the sums
+// and pivots in F, the candidate blocks C of the unit's nsp records and their pivot lists P.  With
+// GB > 1 the unit is one record.
 template <int GB>
 __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int h0, int cnt, int64_t cbase,
-                               int nsp, const CandSrc &C, const PivSrc &P, const FinLds<GB> &F) {
+                               int nsp, const BlockGeo &B, const CandSrc &C, const PivSrc &P,
+                               const FinLds<GB> &F) {
   const int lane = threadIdx.x & 63;
   const int64_t uh0 = (int64_t)u * L.G + h0;
 
@@ -589,35 +612,46 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
   wave_sync();
   if (L.plain) return;  // the uncorrected pass only replaces y and ln N
 
-  // (1c) The range terms of the pivot list entries added back in pivot_prepare (they are in no
-  //      candidate list): sqrt(1 - pi) w |v - yhat| / l, exactly.
+  // (1c) The range terms of the pivot list entries that were added back (they are in no candidate
+  //      list): sqrt(1 - pi) w |v - yhat| / l, exactly.  One head: a lane group of 8 per record, so
+  //      the records' value rows load together; several heads: a lane group per head.
   {
-    const int h = lane >> 3, j = lane & 7;
-    const bool act = h < GB;
-    const int hh = act ? h : 0;
+    const int gi = lane >> 3, j = lane & 7;
+    const int hh = GB > 1 && gi < GB ? gi : 0;
     const float *hs = F.hs + hh * kHs;
     const int pk = __float_as_int(hs[kHsPk]);
     const float M = hs[kHsM], il = 1.0f / hs[kHsL];
     const float *yh = F.o + hh * kHeadDim + 16 * j;
     float bmax = 0.0f;
-    for_each_pivot(P, nsp, hh, act, [&](int row, float lgt, float p, int key) {
-      if (key == pk) return;
-      const uint4 *vr = reinterpret_cast<const uint4 *>(L.Vc + (cbase + row) * kHeadDim + 16 * j);
-      const uint4 va = vr[0], vb = vr[1];
-      const uint32_t vw[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
-      float d2 = 0.0f;
+    for (int s0 = 0; s0 < nsp; s0 += GB > 1 ? 1 : 8) {
+      const int s = GB > 1 ? 0 : s0 + gi;
+      const float *pl = P.at(min(s, nsp - 1), hh);
+      const int n = (GB > 1 ? gi < GB : s < nsp) ? __float_as_int(pl[0]) : 0;
+      for (int e = 0; e < kPivMax; ++e) {
+        if (!__any(e < n)) break;
+        const bool have = e < n && s * kPivMax + e != pk;
+        Row16 v;
+        v.load(L.Vc, cbase, have ? __float_as_int(pl[1 + 3 * e]) : 0, j);
+        float d2 = 0.0f;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float a = bf16_lo(vw[t]) - yh[2 * t], b = bf16_hi(vw[t]) - yh[2 * t + 1];
-        d2 = fmaf(a, a, d2);
-        d2 = fmaf(b, b, d2);
+        for (int t = 0; t < 8; ++t) {
+          const float a = bf16_lo(v.w[t]) - yh[2 * t], b = bf16_hi(v.w[t]) - yh[2 * t + 1];
+          d2 = fmaf(a, a, d2);
+          d2 = fmaf(b, b, d2);
+        }
+        d2 += __shfl_xor(d2, 1);
+        d2 += __shfl_xor(d2, 2);
+        d2 += __shfl_xor(d2, 4);
+        if (have)
+          bmax = fmaxf(bmax, sqrtf(1.0f - pl[3 + 3 * e]) * fast_exp2(pl[2 + 3 * e] - M) * sqrtf(d2) * il);
       }
-      d2 += __shfl_xor(d2, 1);
-      d2 += __shfl_xor(d2, 2);
-      d2 += __shfl_xor(d2, 4);
-      bmax = fmaxf(bmax, sqrtf(1.0f - p) * fast_exp2(lgt - M) * sqrtf(d2) * il);
-    });
-    if (act && j == 0) F.hs[h * kHs + kHsLb] = fmaxf(F.hs[h * kHs + kHsLb], bmax);
+    }
+    if (GB == 1) {
+      bmax = wave_max(bmax);
+      if (lane == 0) F.hs[kHsLb] = fmaxf(F.hs[kHsLb], bmax);
+    } else if (gi < GB && j == 0) {
+      F.hs[gi * kHs + kHsLb] = fmaxf(F.hs[gi * kHs + kHsLb], bmax);
+    }
     wave_sync();
   }
 
@@ -641,30 +675,31 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
   for (int h = 0; h < GB; ++h) redo |= (F.hs[h * kHs + kHsRedo] != 0.0f ? 1u : 0u) << h;
 
   // (2) Candidate bounds: a candidate's value f g |v - yhat| / l is at most f g (Vmax + |yhat|)/l.
-  //     Candidate e = ((s nchunk + k) GB + h) kCand + j.
-  const int R = L.split_rows;
+  //     Candidate e = ((s nb + k) GB + h) kCand + j.
   auto decode = [&](int e, int &h, int &row, float &fg, float &ub) -> bool {
     const int j = e % kCand;
     int r = e / kCand;
     h = r % GB;
     r /= GB;
-    const int k = r % L.nchunk, s = r / L.nchunk;
-    if (k * kChunkRows >= min(cnt - s * R, R)) return false;  // no such chunk
+    const int k = r % B.nb, s = r / B.nb;
+    int ra;
+    if (!B.present(s, k, cnt, ra)) return false;
     const float *blk = C.base + s * C.sstride + k * C.kstride + h * C.hstride;
     const float gj = blk[kChG + j];
     if (!(gj > 0.0f)) return false;
-    row = s * R + k * kChunkRows + (int)((__float_as_uint(blk[kChI + j / 2]) >> (16 * (j & 1))) & 0xffffu);
+    row = ra + (int)((__float_as_uint(blk[kChI + j / 2]) >> (16 * (j & 1))) & 0xffffu);
     const float *hs = F.hs + h * kHs;
     fg = scale_of(blk[kChM], hs[kHsM]) * gj / hs[kHsL];
     ub = fg * (blk[kChVmax] + hs[kHsYn]);
     return true;
   };
-  // Chunk block x = (s nchunk + k) GB + h (16-byte aligned), or null for a chunk that is absent.
-  const int nx = nsp * L.nchunk * GB;
+  // Block x = (s nb + k) GB + h (16-byte aligned), or null for a block that is absent.
+  const int nx = nsp * B.nb * GB;
   auto block_at = [&](int x, int &h) -> const float * {
     h = x % GB;
-    const int sk = x / GB, s = sk / L.nchunk, k = sk - s * L.nchunk;
-    if (x >= nx || k * kChunkRows >= min(cnt - s * R, R)) return nullptr;
+    const int sk = x / GB, s = sk / B.nb, k = sk - s * B.nb;
+    int ra;
+    if (x >= nx || !B.present(s, k, cnt, ra)) return nullptr;
     return C.base + s * C.sstride + k * C.kstride + h * C.hstride;
   };
   // One lane per block: candidate j's bound is g_j F with F = f (Vmax + |yhat|) / l, so the
@@ -821,25 +856,22 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
   //     rescanned row by row.
   const float scale2 = L.scale * kLog2e;
   for (int x0 = 0; x0 < nx; x0 += 64) {
-    const int x = x0 + lane;  // (s nchunk + k) GB + h
+    int hx;
+    const float *bx = block_at(x0 + lane, hx);
     bool need = false;
-    if (x < nx) {
-      const int h = x % GB, sk = x / GB, s = sk / L.nchunk, k = sk % L.nchunk;
-      if (k * kChunkRows < min(cnt - s * R, R)) {
-        const float *blk = C.base + s * C.sstride + k * C.kstride + h * C.hstride;
-        const float *hs = F.hs + h * kHs;
-        const float ub = scale_of(blk[kChM], hs[kHsM]) * (blk[kChA] + blk[kChB] * hs[kHsYn]) / hs[kHsL];
-        need = ub > hs[kHsLb];
-      }
+    if (bx) {
+      const float *hs = F.hs + hx * kHs;
+      const float ub = scale_of(bx[kChM], hs[kHsM]) * (bx[kChA] + bx[kChB] * hs[kHsYn]) / hs[kHsL];
+      need = ub > hs[kHsLb];
     }
     uint64_t m = __ballot(need);
     if (m) load_q();
     while (m) {
       const int xx = x0 + (int)__builtin_ctzll(m);
       m &= m - 1;
-      const int h = xx % GB, sk = xx / GB, s = sk / L.nchunk, k = sk % L.nchunk;
-      const int ra = s * R + k * kChunkRows;
-      const int rz = min(min(cnt, (s + 1) * R), ra + kChunkRows);
+      const int h = xx % GB, sk = xx / GB, s = sk / B.nb, k = sk % B.nb;
+      int ra, rz;
+      B.rows(s, k, cnt, ra, rz);
       const float *hs = F.hs + h * kHs;
       const float M = hs[kHsM];
       const float *qh = F.o + (GB + h) * kHeadDim;
@@ -854,7 +886,7 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
       const float ai = __uint_as_float(
           ((__float_as_uint(blk[kChAL + (i & 3) / 2 + 2 * (i >> 2)]) >> (16 * (i & 1))) & 0xffffu) << 16);
       const uint64_t lanes = __ballot((lane & 7) == 0 && fk * (ai + bterm) > hs[kHsLb]);
-      // rows in the split's pivot list are in no sum here; their terms were taken in step (1c)
+      // rows in the record's pivot list were taken in step (1c) (the pivot's own in closed form)
       const float *plist = P.at(s, h);
       const int pn = __float_as_int(plist[0]);
       float best = 0.0f;
@@ -1066,7 +1098,7 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
         }
       }
     }
-    if (lane == 0) diag_of(L, u, h0)[1] = (uint32_t)__popc(redo);
+    if (lane == 0) atomicAdd(diag_of(L, u, h0) + 1, (uint32_t)__popc(redo));
     wave_sync();
   }
 
@@ -1097,49 +1129,208 @@ __device__ __forceinline__ void finalize_empty(const AttendLaunch &L, int u, int
   if (lane == 0 && !L.plain) diag_of(L, u, h0)[0] = diag_of(L, u, h0)[1] = 0u;
 }
 
-template <int GB>
-__device__ __forceinline__ void finalize_records(const AttendLaunch &L, int u, int h0, float *s_fin);
+// Rows of one wave of a unit with cnt retained rows.  L.split_rows of them were planned for the
+// longest unit; where the library chose the split, a shorter unit's rows are dealt evenly over the
+// same waves instead (every kernel of the launch computes the same number).
+__device__ __forceinline__ int wave_rows(const AttendLaunch &L, int cnt) {
+  if (!L.balanced) return L.split_rows;
+  const int n = L.nsplit * L.wpg;
+  return max(min(L.split_rows, ((cnt + n - 1) / n + 15) / 16 * 16), kWaveMinRows);
+}
+
+// The sums of one head over nsp records (one per wave of a work-group, in LDS, or one per
+// work-group, in the workspace): the pivot becomes the list entry with the largest logit over all
+// of them, every sum is scaled to the common running max and added up, and every other list entry
+// is added back exactly.  One wave; a lane group of 8 takes every eighth record (16 dims per lane),
+// so eight records' sums and pivot rows are in flight together, and the groups' totals meet at the
+// end in a fixed order.  Unless null, s_extra (2 blocks in LDS, zeroed) receives the entries that
+// were added back as range-term candidates, entry e of record s at candidate 8 s + e (at most 64),
+// their row offsets counted from row_first.
+__device__ __forceinline__ void combine_head(const AttendLaunch &L, int64_t cbase, int nsp,
+                                             const float *rec0, int64_t sstride, const FinLds<1> &F,
+                                             float *s_extra, int row_first) {
+  const int lane = (int)__lane_id(), gi = lane >> 3, j = lane & 7;
+  float mm = -INFINITY, bl = -INFINITY;
+  int bk = 0x7fffffff;
+  for (int s = lane; s < nsp; s += 64) {
+    const float *rec = rec0 + s * sstride;
+    const float4 *p4 = reinterpret_cast<const float4 *>(rec + kRecPiv);
+    float pv[4 * 7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      const float4 v = p4[k];
+      pv[4 * k] = v.x, pv[4 * k + 1] = v.y, pv[4 * k + 2] = v.z, pv[4 * k + 3] = v.w;
+    }
+    mm = fmaxf(mm, rec[kRecM]);
+    const int n = __float_as_int(pv[0]);
+#pragma unroll
+    for (int e = 0; e < kPivMax; ++e) {
+      if (e < n && pv[2 + 3 * e] > bl) {
+        bl = pv[2 + 3 * e];
+        bk = s * kPivMax + e;
+      }
+    }
+  }
+  mm = wave_max(mm);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float ol = __shfl_xor(bl, o);
+    const int ok = __shfl_xor(bk, o);
+    if (ol > bl || (ol == bl && ok < bk)) {
+      bl = ol;
+      bk = ok;
+    }
+  }
+  const float M1 = fmaxf(mm, bl);
+
+  float o16[16], c16[16], la = 0.0f, c0a = 0.0f, c2a = 0.0f;
+#pragma unroll
+  for (int t = 0; t < 16; ++t) o16[t] = c16[t] = 0.0f;
+  for (int s0 = 0; s0 < nsp; s0 += 8) {
+    const int s = s0 + gi;
+    const float *rec = rec0 + min(s, nsp - 1) * sstride;
+    const float4 sc = *reinterpret_cast<const float4 *>(rec);  // m, l, C0, C2
+    const float4 *op = reinterpret_cast<const float4 *>(rec + kRecO + 16 * j);
+    const float4 *cp = reinterpret_cast<const float4 *>(rec + kRecCv + 16 * j);
+    float4 ov[4], cv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ov[k] = op[k], cv[k] = cp[k];
+    const float *pl = rec + kRecPiv;
+    const int n = s < nsp ? __float_as_int(pl[0]) : 0;
+    const float f = s < nsp ? scale_of(sc.x, M1) : 0.0f, f2 = f * f;
+    la = fmaf(f, sc.y, la);
+    c0a = fmaf(f2, sc.z, c0a);
+    c2a = fmaf(f2, sc.w, c2a);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float a[4] = {ov[k].x, ov[k].y, ov[k].z, ov[k].w}, c[4] = {cv[k].x, cv[k].y, cv[k].z, cv[k].w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        o16[4 * k + t] = fmaf(f, a[t], o16[4 * k + t]);
+        c16[4 * k + t] = fmaf(f2, c[t], c16[4 * k + t]);
+      }
+    }
+    for (int e = 0; e < kPivMax; ++e) {
+      if (!__any(e < n)) break;
+      const bool have = e < n && s * kPivMax + e != bk;
+      const int row = have ? __float_as_int(pl[1 + 3 * e]) : 0;
+      Row16 v;
+      v.load(L.Vc, cbase, row, j);
+      const float w = have ? fast_exp2(pl[2 + 3 * e] - M1) : 0.0f;
+      const float cc = have ? (1.0f - pl[3 + 3 * e]) * w * w : 0.0f;
+      float nv = 0.0f;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const float x0 = bf16_lo(v.w[t]), x1 = bf16_hi(v.w[t]);
+        o16[2 * t] = fmaf(w, x0, o16[2 * t]);
+        o16[2 * t + 1] = fmaf(w, x1, o16[2 * t + 1]);
+        c16[2 * t] = fmaf(cc, x0, c16[2 * t]);
+        c16[2 * t + 1] = fmaf(cc, x1, c16[2 * t + 1]);
+        nv = fmaf(x0, x0, nv);
+        nv = fmaf(x1, x1, nv);
+      }
+      nv += __shfl_xor(nv, 1);
+      nv += __shfl_xor(nv, 2);
+      nv += __shfl_xor(nv, 4);
+      la += w;
+      c0a += cc;
+      c2a = fmaf(cc, nv, c2a);
+      if (s_extra && have && j == 0 && cc > 0.0f) {
+        const int x = s * kPivMax + e;
+        float *blk = s_extra + (x / kCand) * kChunkFloats;
+        blk[kChG + x % kCand] = fast_sqrt(cc);
+        reinterpret_cast<uint16_t *>(blk + kChI)[x % kCand] = (uint16_t)(row - row_first);
+        atomicMax(reinterpret_cast<unsigned *>(blk + kChVmax), __float_as_uint(fast_sqrt(nv) * 1.000001f));
+        blk[kChM] = M1;
+      }
+    }
+  }
+  // the eight groups' totals, the same in every lane of a column of lanes
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      o16[t] += __shfl_xor(o16[t], o);
+      c16[t] += __shfl_xor(c16[t], o);
+    }
+    la += __shfl_xor(la, o);
+    c0a += __shfl_xor(c0a, o);
+    c2a += __shfl_xor(c2a, o);
+  }
+  wave_sync();  // F may lie over the records' sums: they are read
+  if (gi == 0) {
+    float4 *op = reinterpret_cast<float4 *>(F.o + 16 * j);
+    float4 *cp = reinterpret_cast<float4 *>(F.o + kHeadDim + 16 * j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      op[k] = make_float4(o16[4 * k], o16[4 * k + 1], o16[4 * k + 2], o16[4 * k + 3]);
+      cp[k] = make_float4(c16[4 * k], c16[4 * k + 1], c16[4 * k + 2], c16[4 * k + 3]);
+    }
+  }
+  if (lane == 0) {
+    F.hs[kHsL] = la;
+    F.hs[kHsC0] = c0a;
+    F.hs[kHsC2] = c2a;
+    F.hs[kHsM] = M1;
+    F.hs[kHsPl] = bl;
+    F.hs[kHsPk] = __int_as_float(bk);
+    if (bl > -INFINITY) {
+      const float *pe = rec0 + (bk / kPivMax) * sstride + kRecPiv + 1 + 3 * (bk % kPivMax);
+      F.hs[kHsPr] = pe[0];
+      F.hs[kHsPp] = pe[2];
+    }
+  }
+  wave_sync();
+}
+
+// LDS of a work-group whose waves share a unit: per (wave, head) a record laid out as in the
+// workspace.  Once a head's records are combined their sums are spent: the totals take the place of
+// wave 0's o and Cv, the finalize's table and list that of wave 1's sums.  Parts with records add
+// two blocks per head for added-back pivots.
+static_assert(kRecCv == kRecO + kHeadDim && kHs + 2 + kListCap <= kRecPiv, "the finalize's state fits");
 
 // One wave per (unit, split, head block).  Lane (g, c): MFMA column c is head slot c (weights for
 // c < GB, variance weights for GB <= c < 2 GB, idle above); g selects the row group.
-// Work-groups: one wave each (L.wpg = 1; units of several splits are then finalized by
-// attend_finalize), or, when a unit is cut into L.wpg = L.nsplit splits, the unit's splits as the
-// waves of one work-group: each writes its split record, counts itself in an LDS word, and the
-// wave that arrives last finalizes the unit from the records (no second launch).  Waves of empty
-// splits leave at once; the only work-group barrier is the one after the counter is cleared,
-// which every wave reaches.
-template <int GB, bool COOP>
-__global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_split_kernel(
+// Work-groups: one wave each (L.wpg = 1), which finalizes a unit that it read whole or writes its
+// split's records; or (SHARED) L.wpg waves that share the rows of a unit, or of one of the unit's
+// L.nsplit parts.  These leave their sums, pivot lists and candidate blocks in LDS; after one
+// barrier wave h takes head h of the block through the combination and then either the finalize
+// (one part: no record, no second launch) or the part's record.  A few units (one layer of a few
+// sequences) thereby occupy the whole chip: with one wave per 256 rows and one wave finalizing a
+// unit, a step on 8 units of 13100 rows took 168 us, 146 of them in that wave.
+template <int GB, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 64 * kUnitWaves : 64, 2) void attend_split_kernel(
     AttendLaunch L, int h0) {
   extern __shared__ float s_lds[];
   const int bid = blockIdx.x;
-  const int wave = COOP ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-  constexpr bool coop = COOP;
-  const int sp = coop ? wave : bid % L.nsplit;
-  const int u = coop ? bid : bid / L.nsplit;
+  const int wave = SHARED ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int part = bid % L.nsplit, u = bid / L.nsplit;
+  const int sp = SHARED ? part * L.wpg + wave : part;
   const int lane = (int)__lane_id();  // recomputed where needed rather than kept live (registers)
   const int g = lane >> 4, c = lane & 15;
-  // this wave's LDS: [nchunk][GB][kChunkFloats] chunk blocks, then [GB][kPivFloats] pivot lists
-  float *s_chunk = s_lds + (coop ? (size_t)wave * (L.nchunk * kChunkFloats + kPivFloats) * GB : 0);
-  int *s_arrived = reinterpret_cast<int *>(s_lds + L.coop_counter);
-  if (coop) {
-    if (threadIdx.x == 0) *s_arrived = 0;
-    __syncthreads();  // before any wave can leave or arrive
-  }
   const int64_t cbase = L.cap_off[u];
   const int64_t cap = L.cap_off[u + 1] - cbase;
   const int64_t held = min((int64_t)L.count[u], cap);
-  const int cnt = (int)min(held, (int64_t)L.nsplit * L.split_rows);
+  const int cnt = (int)min(held, (int64_t)L.seen);
   if (L.status && sp == 0 && h0 == 0 && lane == 0 && !L.plain)
     L.status[u] = ((int64_t)L.count[u] > cap ? EBD_ST_CAP_OVERFLOW : 0u) |
                   (held > (int64_t)cnt ? EBD_ST_BAD_LAYOUT : 0u);
-  const int row0 = sp * L.split_rows;
-  if (row0 >= cnt) {  // empty split: the finalize skips it; an empty unit gets empty outputs
-    if (sp == 0 && (COOP || L.nsplit == 1)) finalize_empty<GB>(L, u, h0);
+  if (cnt == 0) {  // an empty unit gets empty outputs
+    if (sp == 0) finalize_empty<GB>(L, u, h0);
     return;
   }
-  const int nrow = min(cnt - row0, L.split_rows);
-
+  if (sp == 0 && lane == 0 && !L.plain) diag_of(L, u, h0)[0] = diag_of(L, u, h0)[1] = 0u;
+  const int r = wave_rows(L, cnt);
+  const int row0 = sp * r;
+  const int wrow0 = part * L.wpg * r;  // the work-group's first row
+  if (wrow0 >= cnt) return;            // an empty part (all of the work-group's waves): skipped later
+  const int nrow = max(min(cnt - row0, r), 0);
+  // this wave's LDS, per head: (SHARED) its sums as in a record, the pivot list, the chunk blocks
+  constexpr int kSums = SHARED ? kRecPiv : 0;
+  const int hstride = kSums + kPivFloats + L.nchunk * kChunkFloats;
+  float *s_rec = s_lds + (size_t)wave * GB * hstride;
+  float *s_chunk = s_rec + kSums + kPivFloats;
+  if (!SHARED || nrow > 0) {
   const bool isW = c < GB;
   const bool isC = (c >= GB) && (c < 2 * GB);
   const bool active = isW || isC;
@@ -1165,10 +1356,10 @@ __global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_spl
   S.mrun = active ? -1e30f : 0.0f;
   S.s0 = S.s1 = 0.0f;
   S.pl = -INFINITY;
-  float *s_piv = s_chunk + L.nchunk * GB * kChunkFloats;  // [GB][kPivFloats]
-  if (isW && g == 0) {  // empty lists
-    s_piv[c * kPivFloats] = __int_as_float(0);
-    s_piv[c * kPivFloats + kPivLogit] = -INFINITY;
+  float *piv = s_rec + kSums + hs * hstride;  // the pivot list of this lane's head
+  if (isW && g == 0) {                        // empty lists
+    piv[0] = __int_as_float(0);
+    piv[kPivLogit] = -INFINITY;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1196,9 +1387,9 @@ __global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_spl
   constexpr int kChunkTiles = kChunkRows / 16;
   // tile tt of the split, then the flush of its chunk if tt ends one
   auto step = [&](const Tile &T, int tt) {
-    split_tile<(GB > 7)>(S, T, qop, nv0 - 16 * tt, rb0 + 16 * tt, isC, plain, scale2, s_piv, hs, isW);
+    split_tile<(GB > 7)>(S, T, qop, nv0 - 16 * tt, rb0 + 16 * tt, isC, plain, scale2, piv, isW);
     if ((tt + 1) % kChunkTiles == 0)
-      flush_chunk<GB>(S, s_chunk, tt / kChunkTiles, g, c, row0 + (tt / kChunkTiles) * kChunkRows);
+      flush_chunk<GB>(S, s_chunk, hstride, tt / kChunkTiles, g, c, row0 + (tt / kChunkTiles) * kChunkRows);
   };
   int t = 0;
   for (; t + 3 <= ntile; t += 3) {
@@ -1214,7 +1405,7 @@ __global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_spl
   // every chunk is flushed once: full ones where they end, a partial last one here
   const int nck = (ntile + kChunkTiles - 1) / kChunkTiles;
   if (ntile % kChunkTiles != 0)
-    flush_chunk<GB>(S, s_chunk, nck - 1, g, c, row0 + (nck - 1) * kChunkRows);
+    flush_chunk<GB>(S, s_chunk, hstride, nck - 1, g, c, row0 + (nck - 1) * kChunkRows);
 
   // ---- epilogue ------------------------------------------------------------------------------
   float s0 = S.s0, s1 = S.s1;
@@ -1222,10 +1413,10 @@ __global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_spl
   s0 += __shfl_xor(s0, 32);
   s1 += __shfl_xor(s1, 16);
   s1 += __shfl_xor(s1, 32);
-  if (!COOP && L.nsplit == 1) {
+  if (!SHARED && L.nsplit == 1) {
     // The unit is this one split: its sums go to LDS beside the chunk blocks and the wave
     // finalizes its heads itself (no record, no second launch).
-    FinLds<GB> F(s_piv + GB * kPivFloats);
+    FinLds<GB> F(s_lds + GB * hstride);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int slot = 4 * g + i;
@@ -1242,175 +1433,112 @@ __global__ __launch_bounds__(COOP ? 64 * kCoopMaxSplits : 64, 2) void attend_spl
       F.hs[(c - GB) * kHs + kHsC0] = s0;
       F.hs[(c - GB) * kHs + kHsC2] = s1;
     }
-    if (lane == 0 && !L.plain) diag_of(L, u, h0)[0] = diag_of(L, u, h0)[1] = 0u;
     wave_sync();
-    const CandSrc C{s_chunk, 0, GB * kChunkFloats, kChunkFloats};
-    const PivSrc P{s_piv, 0, kPivFloats};
-    pivot_prepare<GB>(L, cbase, 1, P, F);
-    finalize_block<GB>(L, u, h0, cnt, cbase, 1, C, P, F);
+    const BlockGeo B{r, 1, L.nchunk, L.nchunk};
+    const CandSrc C{s_chunk, 0, kChunkFloats, hstride};
+    const PivSrc P{s_rec, 0, hstride};
+    pivot_prepare<GB>(L, cbase, P, F);
+    finalize_block<GB>(L, u, h0, cnt, cbase, 1, B, C, P, F);
     return;
   }
-  // Several splits: this one's record (sums from registers, chunk blocks from LDS).
-  float *rec_base = L.part + (((int64_t)u * L.nsplit + sp) * L.G + h0) * L.rec;
-  // o (slots < GB) and Cv (slots GB .. 2GB-1): lane (g, c) holds slots 4g + i, dims 8c .. 8c + 7
+  // Several waves per unit: this one's sums, as a record in LDS or, for a one-wave work-group, in
+  // the workspace.  o (slots < GB) and Cv (slots GB .. 2GB-1): lane (g, c) holds slots 4g + i,
+  // dims 8c .. 8c + 7.
+  float *rec_base = SHARED ? s_rec : L.part + (((int64_t)u * L.nsplit + sp) * L.G + h0) * L.rec;
+  const int rstride = SHARED ? hstride : L.rec;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int slot = 4 * g + i;
     if (slot < 2 * GB) {
       const int hh = slot < GB ? slot : slot - GB;
-      float4 *dst = reinterpret_cast<float4 *>(rec_base + (int64_t)hh * L.rec +
+      float4 *dst = reinterpret_cast<float4 *>(rec_base + (int64_t)hh * rstride +
                                                (slot < GB ? kRecO : kRecCv) + 8 * c);
       dst[0] = make_float4(S.acc[0][i], S.acc[1][i], S.acc[2][i], S.acc[3][i]);
       dst[1] = make_float4(S.acc[4][i], S.acc[5][i], S.acc[6][i], S.acc[7][i]);
     }
   }
   if (g == 0 && isW) {
-    float *rec = rec_base + (int64_t)c * L.rec;
+    float *rec = rec_base + (int64_t)c * rstride;
     rec[kRecM] = S.mrun;
     rec[kRecL] = s0;
   } else if (g == 0 && isC) {
-    float *rec = rec_base + (int64_t)(c - GB) * L.rec;
+    float *rec = rec_base + (int64_t)(c - GB) * rstride;
     rec[kRecC0] = s0;
     rec[kRecC2] = s1;
   }
-  wave_sync();  // the chunk blocks and the pivot lists are in LDS
-  for (int e = lane; e < GB * kPivFloats; e += 64)
-    rec_base[(int64_t)(e / kPivFloats) * L.rec + kRecPiv + e % kPivFloats] = s_piv[e];
-  const int nblk = nck * GB * kChunkFloats;
-  for (int e = lane; e < nblk; e += 64) {
-    const int k = e / (GB * kChunkFloats), r = e % (GB * kChunkFloats);
-    const int hh = r / kChunkFloats, j = r % kChunkFloats;
-    rec_base[(int64_t)hh * L.rec + kRecChunks + k * kChunkFloats + j] = s_chunk[e];
-  }
-  if (!COOP) return;
-  // The record is complete (the release makes it visible to the work-group's other waves before
-  // the count moves); the last of the unit's nsp waves to arrive finalizes.  Its FinLds reuses
-  // the LDS of the splits, whose waves are all done with it by then.
-  const int nsp = (cnt + L.split_rows - 1) / L.split_rows;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  int before = 0;
-  if (lane == 0) before = __hip_atomic_fetch_add(s_arrived, 1, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-  before = __builtin_amdgcn_readfirstlane(before);
-  if (before != nsp - 1) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  finalize_records<GB>(L, u, h0, s_lds);
-}
-
-// attend_finalize: one wave per (unit, head block) when units are cut into several splits.  The
-// split records are combined into LDS, then the unit is finalized like a fused split, reading
-// the candidate blocks from the records (a lane per block, whole blocks as float4).  Every global
-// read of the records is issued in batches, so the wave waits on a handful of round trips rather
-// than one per split or candidate.
-// Float offset of the split scale factors in the finalize's LDS (after FinLds).
-template <int GB>
-__host__ __device__ constexpr size_t fin_scale_off() {
-  return FinLds<GB>::bytes() / sizeof(float);
-}
-
-// The finalize of unit u from its split records, by one wave (s_fin: FinLds, then the split
-// scale factors).
-template <int GB>
-__device__ __forceinline__ void finalize_records(const AttendLaunch &L, int u, int h0, float *s_fin) {
-  const int lane = threadIdx.x & 63;
-  const int64_t cbase = L.cap_off[u];
-  const int64_t cap = L.cap_off[u + 1] - cbase;
-  const int cnt = (int)min(min((int64_t)L.count[u], cap), (int64_t)L.nsplit * L.split_rows);
-  if (cnt == 0) {
-    finalize_empty<GB>(L, u, h0);
+  if (!SHARED) {
+    wave_sync();  // the chunk blocks and the pivot lists are in LDS
+    const int nel = kPivFloats + nck * kChunkFloats;
+    for (int hh = 0; hh < GB; ++hh)
+      for (int e = lane; e < nel; e += 64)
+        rec_base[(int64_t)hh * L.rec + kRecPiv + e] = s_rec[hh * hstride + e];
     return;
   }
-  if (lane == 0 && !L.plain) diag_of(L, u, h0)[0] = diag_of(L, u, h0)[1] = 0u;
-  wave_sync();  // the zeroed words are in place before the finalize's own updates
-  const int nsp = (cnt + L.split_rows - 1) / L.split_rows;
-  const float *rec0 = L.part + ((int64_t)u * L.nsplit * L.G + h0) * L.rec;  // (s, h) at s G rec + h rec
-  const int64_t sstride = (int64_t)L.G * L.rec;
-  FinLds<GB> F(s_fin);
-  float *fsc = s_fin + fin_scale_off<GB>();  // [nsplit][GB]: scale of (s, h)
-
-  // Scalars (M, l, C0, C2) of every (split, head): one float4 per lane and head, all in flight.
-  for (int s0 = 0; s0 < nsp; s0 += 64) {
-    const int sl = s0 + lane;
-    float4 r[GB];
-#pragma unroll
-    for (int h = 0; h < GB; ++h)
-      r[h] = sl < nsp ? *reinterpret_cast<const float4 *>(rec0 + sl * sstride + h * L.rec + kRecM)
-                      : make_float4(-INFINITY, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-    for (int h = 0; h < GB; ++h) {
-      if (sl < nsp) fsc[sl * GB + h] = r[h].x;  // the split's running max, for now
-      const float M = wave_max(r[h].x);
-      const float mo = s0 == 0 ? -INFINITY : F.hs[h * kHs + kHsM];  // earlier batches
-      const float Mn = fmaxf(M, mo);
-      const float f = scale_of(r[h].x, Mn);
-      float l = wave_sum(f * r[h].y), c0 = wave_sum(f * f * r[h].z), c2 = wave_sum(f * f * r[h].w);
-      if (lane == 0) {
-        const float fo = s0 == 0 ? 0.0f : scale_of(mo, Mn);
-        F.hs[h * kHs + kHsM] = Mn;
-        F.hs[h * kHs + kHsL] = l + (s0 == 0 ? 0.0f : fo * F.hs[h * kHs + kHsL]);
-        F.hs[h * kHs + kHsC0] = c0 + (s0 == 0 ? 0.0f : fo * fo * F.hs[h * kHs + kHsC0]);
-        F.hs[h * kHs + kHsC2] = c2 + (s0 == 0 ? 0.0f : fo * fo * F.hs[h * kHs + kHsC2]);
+  }  // the wave has rows
+  if constexpr (SHARED) {
+    // the diagnostic words' zeros have left for memory before any wave can count into them
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __syncthreads();
+    const int nact = min(L.wpg, (cnt - wrow0 + r - 1) / r);  // waves that had rows
+    for (int h = wave; h < GB; h += L.wpg) {
+      float *rec0 = s_lds + h * hstride;
+      const FinLds<1> F(rec0 + kRecO, rec0 + GB * hstride);
+      if (L.nsplit == 1) {
+        combine_head(L, cbase, nact, rec0, (int64_t)GB * hstride, F, nullptr, 0);
+        const BlockGeo B{r, 1, L.nchunk, L.nchunk};
+        const CandSrc C{rec0 + kRecChunks, (int64_t)GB * hstride, kChunkFloats, 0};
+        const PivSrc P{rec0 + kRecPiv, (int64_t)GB * hstride, 0};
+        finalize_block<1>(L, u, h0 + h, cnt, cbase, nact, B, C, P, F);
+        continue;
       }
+      // the part's record: the combined sums, its pivot alone in the list, every wave's blocks,
+      // then the blocks of the pivots that were added back
+      float *s_extra = s_lds + (L.wpg * GB) * hstride + h * 2 * kChunkFloats;
+      for (int e = lane; e < 2 * kChunkFloats; e += 64) s_extra[e] = 0.0f;
       wave_sync();
-    }
-  }
-  // the scale of every split to the combined max
-  for (int e = lane; e < nsp * GB; e += 64) fsc[e] = scale_of(fsc[e], F.hs[(e % GB) * kHs + kHsM]);
-  wave_sync();
-
-  // o and Cv: two dims per lane, every slot of SP splits in flight at once.
-  {
-    constexpr int SP = GB <= 4 ? 4 : 2;
-    float2 acc[2 * GB];
-#pragma unroll
-    for (int slot = 0; slot < 2 * GB; ++slot) acc[slot] = make_float2(0.0f, 0.0f);
-    for (int sp = 0; sp < nsp; sp += SP) {
-      float2 a[SP][2 * GB];
-#pragma unroll
-      for (int q = 0; q < SP; ++q)
-#pragma unroll
-        for (int slot = 0; slot < 2 * GB; ++slot) {
-          const int h = slot < GB ? slot : slot - GB;
-          const int off = slot < GB ? kRecO : kRecCv;
-          a[q][slot] = sp + q < nsp ? reinterpret_cast<const float2 *>(
-                                          rec0 + (sp + q) * sstride + h * L.rec + off)[lane]
-                                    : make_float2(0.0f, 0.0f);
-        }
-#pragma unroll
-      for (int q = 0; q < SP; ++q) {
-        if (sp + q >= nsp) break;
-#pragma unroll
-        for (int slot = 0; slot < 2 * GB; ++slot) {
-          const int h = slot < GB ? slot : slot - GB;
-          float f = fsc[(sp + q) * GB + h];
-          if (slot >= GB) f *= f;
-          acc[slot].x = fmaf(f, a[q][slot].x, acc[slot].x);
-          acc[slot].y = fmaf(f, a[q][slot].y, acc[slot].y);
-        }
+      combine_head(L, cbase, nact, rec0, (int64_t)GB * hstride, F, s_extra, wrow0);
+      float *rec = L.part + (((int64_t)u * L.nsplit + part) * L.G + h0 + h) * L.rec;
+      for (int e = lane; e < 2 * kHeadDim; e += 64) rec[kRecO + e] = F.o[e];
+      if (lane == 0) {
+        *reinterpret_cast<float4 *>(rec) =
+            make_float4(F.hs[kHsM], F.hs[kHsL], F.hs[kHsC0], F.hs[kHsC2]);
+        const bool piv = F.hs[kHsPl] > -INFINITY;
+        *reinterpret_cast<float4 *>(rec + kRecPiv) =
+            make_float4(__int_as_float(piv ? 1 : 0), F.hs[kHsPr], F.hs[kHsPl], F.hs[kHsPp]);
       }
+      const int nbw = L.nchunk * kChunkFloats;  // floats of one wave's blocks
+      for (int w = 0; w < nact; ++w) {
+        const float *src = rec0 + (int64_t)w * GB * hstride + kRecChunks;
+        for (int e = lane; e < nbw; e += 64) rec[kRecChunks + w * nbw + e] = src[e];
+      }
+      for (int e = lane; e < 2 * kChunkFloats; e += 64) rec[kRecChunks + L.wpg * nbw + e] = s_extra[e];
     }
-#pragma unroll
-    for (int slot = 0; slot < 2 * GB; ++slot)
-      reinterpret_cast<float2 *>(F.o + slot * kHeadDim)[lane] = acc[slot];
   }
-
-  wave_sync();
-  const CandSrc C{rec0 + kRecChunks, sstride, kChunkFloats, L.rec};
-  const PivSrc P{rec0 + kRecPiv, sstride, L.rec};
-  pivot_prepare<GB>(L, cbase, nsp, P, F);
-  finalize_block<GB>(L, u, h0, cnt, cbase, nsp, C, P, F);
 }
 
-template <int GB>
+// attend_finalize: one wave per (unit, head) when units are cut into several records: combined
+// with a lane group per record, then finalized like a unit whose sums are in LDS, the candidate
+// blocks read from the records (a lane per block, whole blocks as float4).  With one wave for a
+// unit's whole head block and the records' pivots walked one after another it took 32 us for 256
+// units of 6 records and 146 us for 8 units of 52.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void attend_finalize_kernel(AttendLaunch L, int h0) {
+void attend_finalize_kernel(AttendLaunch L) {
   extern __shared__ float s_fin[];
-  finalize_records<GB>(L, blockIdx.x, h0, s_fin);
-}
-
-template <int GB>
-size_t attend_finalize_lds(const AttendLaunch &L) {
-  return (fin_scale_off<GB>() + (size_t)L.nsplit * GB) * sizeof(float);
+  const int u = blockIdx.x / L.G, h = blockIdx.x % L.G;
+  const int64_t cbase = L.cap_off[u];
+  const int64_t cap = L.cap_off[u + 1] - cbase;
+  const int cnt = (int)min(min((int64_t)L.count[u], cap), (int64_t)L.seen);
+  if (cnt == 0) return;  // its outputs are written already
+  const int r = wave_rows(L, cnt);
+  const int nsp = (cnt + r * L.wpg - 1) / (r * L.wpg);
+  const float *rec0 = L.part + ((int64_t)u * L.nsplit * L.G + h) * L.rec;
+  const int64_t sstride = (int64_t)L.G * L.rec;
+  const FinLds<1> F(s_fin);
+  combine_head(L, cbase, nsp, rec0, sstride, F, nullptr, 0);
+  const BlockGeo B{r, L.wpg, L.nchunk, L.wpg * L.nchunk + (L.wpg > 1 ? 2 : 0)};
+  const CandSrc C{rec0 + kRecChunks, sstride, kChunkFloats, 0};
+  const PivSrc P{rec0 + kRecPiv, sstride, 0};
+  finalize_block<1>(L, u, h, cnt, cbase, nsp, B, C, P, F);
 }
 
 size_t attend_workspace_bytes(int32_t U, int32_t nsplit, int32_t G, int32_t split_rows) {
@@ -1421,78 +1549,46 @@ size_t attend_workspace_bytes(int32_t U, int32_t nsplit, int32_t G, int32_t spli
                     sizeof(float);
 }
 
-size_t attend_finalize_lds_gb(const AttendLaunch &L, int gb) {
-  switch (gb) {
-    case 1: return attend_finalize_lds<1>(L);
-    case 2: return attend_finalize_lds<2>(L);
-    case 3: return attend_finalize_lds<3>(L);
-    case 4: return attend_finalize_lds<4>(L);
-    case 5: return attend_finalize_lds<5>(L);
-    case 6: return attend_finalize_lds<6>(L);
-    case 7: return attend_finalize_lds<7>(L);
-    default: return attend_finalize_lds<8>(L);
-  }
-}
-
-// Float offset of the arrival count of a work-group of a unit's splits: after the splits' own
-// LDS and after the finalize's, which reuses the splits' space.
-int32_t attend_coop_counter(const AttendLaunch &L, int gb) {
-  const size_t part = ((size_t)L.nchunk * kChunkFloats + kPivFloats) * gb;
-  const size_t fin = attend_finalize_lds_gb(L, gb) / sizeof(float);
-  const size_t need = part * (size_t)L.wpg > fin ? part * (size_t)L.wpg : fin;
-  return (int32_t)((need + 3) / 4 * 4);
-}
-
-size_t attend_split_lds(const AttendLaunch &L, int gb) {
-  size_t b = ((size_t)L.nchunk * kChunkFloats + kPivFloats) * gb * sizeof(float);
-  if (L.nsplit > 1 && L.wpg > 1) return ((size_t)attend_coop_counter(L, gb) + 4) * sizeof(float);
-  if (L.nsplit == 1) {
-    size_t f = 0;
-    switch (gb) {
-      case 1: f = FinLds<1>::bytes(); break;
-      case 2: f = FinLds<2>::bytes(); break;
-      case 3: f = FinLds<3>::bytes(); break;
-      case 4: f = FinLds<4>::bytes(); break;
-      case 5: f = FinLds<5>::bytes(); break;
-      case 6: f = FinLds<6>::bytes(); break;
-      case 7: f = FinLds<7>::bytes(); break;
-      default: f = FinLds<8>::bytes(); break;
-    }
-    b += f;
-  }
-  return b;
+// LDS of a one-wave work-group: the pivot lists and chunk blocks, and for a unit that it reads
+// whole the finalize's state.
+size_t attend_part_lds_bytes(int32_t split_rows, int gb) {
+  return ((size_t)attend_chunks(split_rows) * kChunkFloats + kPivFloats) * gb * sizeof(float);
 }
 
 size_t attend_fused_lds_bytes(int32_t split_rows, int gb) {
-  AttendLaunch L{};
-  L.nsplit = 1;
-  L.wpg = 1;
-  L.nchunk = attend_chunks(split_rows);
-  return attend_split_lds(L, gb);
+  size_t f = 0;
+  switch (gb) {
+    case 1: f = FinLds<1>::bytes(); break;
+    case 2: f = FinLds<2>::bytes(); break;
+    case 3: f = FinLds<3>::bytes(); break;
+    case 4: f = FinLds<4>::bytes(); break;
+    case 5: f = FinLds<5>::bytes(); break;
+    case 6: f = FinLds<6>::bytes(); break;
+    case 7: f = FinLds<7>::bytes(); break;
+    default: f = FinLds<8>::bytes(); break;
+  }
+  return attend_part_lds_bytes(split_rows, gb) + f;
 }
 
-size_t attend_part_lds_bytes(int32_t split_rows, int gb) {
-  AttendLaunch L{};
-  L.nsplit = 2;
-  L.wpg = 1;
-  L.nchunk = attend_chunks(split_rows);
-  return attend_split_lds(L, gb);
+// LDS of a work-group whose waves share a unit.
+size_t attend_shared_lds_bytes(int32_t wave_rows, int wpg, int gb, bool records) {
+  return ((size_t)wpg * gb * (kRecChunks + (size_t)attend_chunks(wave_rows) * kChunkFloats) +
+          (records ? (size_t)gb * 2 * kChunkFloats : 0)) * sizeof(float);
 }
 
-hipError_t launch_attend_split(const AttendLaunch &L0, hipStream_t s) {
-  if (L0.wpg != 1 && (L0.wpg != L0.nsplit || L0.wpg > kCoopMaxSplits)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((int64_t)L0.U * (L0.wpg > 1 ? 1 : L0.nsplit))),
-      block(kAttendThreads * L0.wpg);
-  for (int h0 = 0; h0 < L0.G; h0 += kHeadBlock) {
-    const int gb = min(kHeadBlock, L0.G - h0);
-    AttendLaunch L = L0;
-    L.coop_counter = L.wpg > 1 ? attend_coop_counter(L, gb) : 0;
-    const size_t lds = attend_split_lds(L, gb);
-    const bool coop = L.wpg > 1;
+hipError_t launch_attend_split(const AttendLaunch &L, hipStream_t s) {
+  const bool shared = L.wpg > 1;
+  if (L.wpg < 1 || L.wpg > kUnitWaves) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((int64_t)L.U * L.nsplit)), block(kAttendThreads * L.wpg);
+  for (int h0 = 0; h0 < L.G; h0 += kHeadBlock) {
+    const int gb = min(kHeadBlock, L.G - h0);
+    const size_t lds = shared          ? attend_shared_lds_bytes(L.split_rows, L.wpg, gb, L.nsplit > 1)
+                       : L.nsplit == 1 ? attend_fused_lds_bytes(L.split_rows, gb)
+                                       : attend_part_lds_bytes(L.split_rows, gb);
     switch (gb) {
 #define EBD_SPLIT(N)                                                                              \
   case N:                                                                                         \
-    if (coop)                                                                                     \
+    if (shared)                                                                                   \
       hipLaunchKernelGGL((attend_split_kernel<N, true>), grid, block, lds, s, L, h0);             \
     else                                                                                          \
       hipLaunchKernelGGL((attend_split_kernel<N, false>), grid, block, lds, s, L, h0);            \
@@ -1514,29 +1610,9 @@ hipError_t launch_attend_split(const AttendLaunch &L0, hipStream_t s) {
 }
 
 hipError_t launch_attend_finalize(const AttendLaunch &L, hipStream_t s) {
-  const dim3 grid((unsigned)L.U), block(64);
-  for (int h0 = 0; h0 < L.G; h0 += kHeadBlock) {
-    const int gb = min(kHeadBlock, L.G - h0);
-    switch (gb) {
-#define EBD_FIN(N)                                                                             \
-  case N:                                                                                      \
-    hipLaunchKernelGGL(attend_finalize_kernel<N>, grid, block, attend_finalize_lds<N>(L), s, L, \
-                       h0);                                                                    \
-    break;
-      EBD_FIN(1)
-      EBD_FIN(2)
-      EBD_FIN(3)
-      EBD_FIN(4)
-      EBD_FIN(5)
-      EBD_FIN(6)
-      EBD_FIN(7)
-      default: EBD_FIN(8)
-#undef EBD_FIN
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipLaunchKernelGGL(attend_finalize_kernel, dim3((unsigned)((int64_t)L.U * L.G)), dim3(64),
+                     FinLds<1>::bytes(), s, L);
+  return hipGetLastError();
 }
 
 }  // namespace ebd

@@ -119,6 +119,56 @@ int32_t attend_nsplit(const ebd_attend_params *p, int32_t sr) {
   return (int32_t)(ns > 0 ? ns : 1);
 }
 
+// How a launch is cut: `parts` work-groups per unit, `wpg` waves each, `rows` retained rows per wave.
+struct AttendPlan {
+  int32_t parts, wpg, rows, balanced;
+};
+
+// Floats of a record of a part of `wpg` waves of `rows` rows: the sums and the part's pivot, the
+// waves' chunk blocks, two blocks of added-back pivots.
+int64_t part_record_floats(int32_t rows, int32_t wpg) {
+  return wpg > 1 ? kRecChunks + (int64_t)kChunkFloats * (wpg * attend_chunks(rows) + 2)
+                 : attend_record_floats(rows);
+}
+
+// The workspace is sized by attend_split_rows (sr rows, ns splits); the launch uses at most that.
+//  * The caller's split_rows: one wave per split; up to eight splits share a work-group.
+//  * Many units (one split each): a wave per unit.
+//  * Otherwise a work-group of up to eight waves shares a unit, as many as keep 2048 waves resident
+//    (8 waves up to 256 units, 4 up to 512, 2 up to 1024 and above).  One work-group per unit
+//    needs no record and no second launch, and its waves read 16 rows in about 0.8 us, so it is kept
+//    to 3584 rows (28 tiles per wave) and for 256 units or more, where the memory is busy anyway;
+//    longer units of smaller launches are cut into parts until 256 work-groups run, at least 96
+//    rows per wave.
+AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
+  const int64_t cap = (int64_t)ns * sr, U = p->num_units;  // every plan covers the same rows
+  const int gb = std::min(p->group, kHeadBlock);
+  if (p->split_rows > 0) {
+    if (ns > 1 && ns <= kUnitWaves && attend_shared_lds_bytes(sr, ns, gb, false) <= kUnitLdsMax)
+      return {1, ns, sr, 0};
+    return {ns, 1, sr, 0};
+  }
+  if (U * ((p->group + kHeadBlock - 1) / kHeadBlock) >= kSplitWaves && ns == 1) return {1, 1, sr, 0};
+  if (cap <= kWaveMinRows) return {1, 1, sr, 0};
+  const int32_t wpg = U <= 256 ? 8 : U <= 512 ? 4 : 2;
+  const size_t lds_max = kUnitLdsMax * (size_t)wpg / kUnitWaves;  // so that 8 waves share a CU
+  int64_t parts = 1;
+  if (U < 256 && cap > kUnitRowsMax)
+    parts = std::max<int64_t>(1, std::min<int64_t>(256 / U, cap / (kPartWaveRows * wpg)));
+  const int64_t room = (int64_t)ns * attend_record_floats(sr);  // per (unit, head)
+  // fewest parts that the LDS allows, at least the wanted ones, then fewer while records exceed
+  // the workspace
+  auto rows_of = [&](int64_t n) { return (int32_t)(((cap + n * wpg - 1) / (n * wpg) + 15) / 16 * 16); };
+  while (parts < kMaxSplits && (rows_of(parts) > kSplitRowsLimit ||
+                                attend_shared_lds_bytes(rows_of(parts), wpg, gb, parts > 1) > lds_max))
+    ++parts;
+  while (parts > 1 && parts * part_record_floats(rows_of(parts), wpg) > room) --parts;
+  const int32_t rows = rows_of(parts);
+  if (rows > kSplitRowsLimit || attend_shared_lds_bytes(rows, wpg, gb, parts > 1) > lds_max || parts >= kMaxSplits)
+    return {ns, 1, sr, 0};  // records of one-wave splits
+  return {(int32_t)parts, wpg, std::max(rows, kWaveMinRows), 1};
+}
+
 // Rows per scores split: as for attention, one split per unit when the units give enough
 // waves, else equal splits (at least 256 rows, at most 8192).
 int32_t scores_split_rows(const ebd_scores_params *p) {
@@ -205,19 +255,17 @@ ebd_status attend_launch(const ebd_attend_params *p, const uint16_t *q, const ui
                          void *workspace, void *stream, bool timing) {
   const int32_t sr = attend_split_rows(p);
   const int32_t nsplit = attend_nsplit(p, sr);
+  const AttendPlan plan = attend_plan(p, sr, nsplit);
   AttendLaunch L;
   L.U = p->num_units;
   L.G = p->group;
-  L.nsplit = nsplit;
-  // a unit of 2..4 splits runs them as one work-group's waves, the last of which finalizes
-  L.wpg = (nsplit > 1 && nsplit <= kCoopMaxSplits &&
-           (size_t)nsplit * attend_part_lds_bytes(sr, std::min(p->group, kHeadBlock)) <= kCoopLdsMax)
-              ? nsplit
-              : 1;
-  L.coop_counter = 0;
-  L.split_rows = sr;
-  L.nchunk = attend_chunks(sr);
-  L.rec = attend_record_floats(sr);
+  L.nsplit = plan.parts;
+  L.wpg = plan.wpg;
+  L.split_rows = plan.rows;
+  L.seen = (int32_t)std::min<int64_t>((int64_t)sr * nsplit, INT32_MAX);
+  L.balanced = plan.balanced;
+  L.nchunk = attend_chunks(plan.rows);
+  L.rec = (int32_t)part_record_floats(plan.rows, plan.wpg);
   L.nhb = (p->group + kHeadBlock - 1) / kHeadBlock;
   L.cap_off = p->cap_off;
   L.count = count;
@@ -246,7 +294,7 @@ ebd_status attend_launch(const ebd_attend_params *p, const uint16_t *q, const ui
     const hipError_t e1 = timing ? timed("attend_split", s, [&] { return launch_attend_split(L, s); })
                                  : launch_attend_split(L, s);
     if (e1 != hipSuccess) return EBD_ERR_HIP;
-    if (L.nsplit > 1 && L.wpg == 1) {
+    if (L.nsplit > 1) {
       const hipError_t e2 =
           timing ? timed("attend_finalize", s, [&] { return launch_attend_finalize(L, s); })
                  : launch_attend_finalize(L, s);

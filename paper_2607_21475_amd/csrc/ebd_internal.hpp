@@ -16,15 +16,18 @@ constexpr int kSelectRegThreads = 128;       // evict_select_reg: two waves per 
 constexpr int kCopyThreads = 256;            // evict_copy: 16 lanes per 256-byte row
 constexpr int kCopyRows = 128;               // retained rows per evict_copy work-group
 
-constexpr int kAttendThreads = 64;   // one wave per (unit, split, head block); wpg waves per work-group
+constexpr int kAttendThreads = 64;   // threads of a wave; wpg waves per attention work-group
 constexpr int kHeadBlock = 8;        // query heads handled together (MFMA rows: 8 weight + 8 variance)
 constexpr int kSplitMaxRows = 4096;  // default split length cap (bounds the launch's tail)
 constexpr int kSplitMinRows = 256;   // default split length floor
 constexpr int kSplitWaves = 1536;    // default: cut units until the launch has this many waves
 constexpr int kSplitRowsLimit = 8192;  // largest split a caller may ask for (LDS of one wave)
 constexpr int kMaxSplits = 4096;       // splits per unit (the finalize keeps a scale per split and head in LDS)
-constexpr int kCoopMaxSplits = 4;      // units of 2..4 splits run them as the waves of one work-group
-constexpr size_t kCoopLdsMax = 61440;  // ... and their LDS stays within 60 KB per work-group
+constexpr int kUnitWaves = 8;          // most waves of a work-group that shares a unit (two per SIMD)
+constexpr size_t kUnitLdsMax = 155648;  // LDS of such a work-group of 8 waves, alone on its CU (of 160 KB)
+constexpr int kUnitRowsMax = 3584;     // units of at most this many rows stay one work-group
+constexpr int kWaveMinRows = 32;       // fewest rows worth a wave of its own
+constexpr int kPartWaveRows = 96;      // ... when a unit is cut into parts with records
 constexpr size_t kSplitLdsBudget = 20480;  // LDS of one split wave at two waves per SIMD (160 KB / 8)
 constexpr int kResidentWaves = 2048;       // attention waves resident at once: two per SIMD, 256 CUs
 constexpr int kScoresMaxQueries = 64;  // queries per ebd_scores call (four MFMA blocks)
@@ -86,10 +89,13 @@ struct EvictLaunch {
 };
 
 struct AttendLaunch {
-  int32_t U, G, nsplit, split_rows, nhb;
-  int32_t wpg;           // waves per work-group: 1, or nsplit (a unit's splits in one work-group)
-  int32_t coop_counter;  // float offset in LDS of the arrival count (wpg > 1; set per head block)
-  int32_t nchunk, rec;  // chunks per split, floats per record
+  int32_t U, G, nhb;
+  int32_t nsplit;       // work-groups (parts) per unit: one record each when there are several
+  int32_t wpg;          // waves per work-group
+  int32_t split_rows;   // rows per wave, as planned for the longest unit
+  int32_t seen;         // rows of a unit that the launch covers
+  int32_t balanced;     // 1: shorter units deal their rows evenly over the same waves
+  int32_t nchunk, rec;  // chunk blocks per wave, floats per record
   int32_t plain;        // 1: the uncorrected pass (no offset; writes y and lse only)
   const int64_t *cap_off;
   const int32_t *count;
@@ -150,6 +156,8 @@ constexpr int64_t kMaxBlocks = 8192;  // blocks per unit of ebd_block_contributi
 size_t attend_workspace_bytes(int32_t U, int32_t nsplit, int32_t G, int32_t split_rows);
 size_t attend_fused_lds_bytes(int32_t split_rows, int gb);  // LDS of a split that also finalizes
 size_t attend_part_lds_bytes(int32_t split_rows, int gb);   // LDS of one split of several
+// LDS of waves that share a unit (records: or a part of one)
+size_t attend_shared_lds_bytes(int32_t wave_rows, int wpg, int gb, bool records);
 size_t scores_workspace_bytes(int32_t U, int32_t nsplit, int32_t W);
 
 // The attention entry points' shared parts (ebd_api.cpp): argument checks (need = workspace
