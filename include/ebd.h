@@ -126,10 +126,10 @@ typedef struct ebd_evict_params {
  *     pi_full [rows] fp32 or NULL   pi of every full-cache position
  *     status [U] uint32             EBD_ST_* bits
  *   workspace: at least ebd_workspace_size(EBD_WS_EVICT, p) bytes, 256-byte aligned
- *   (currently reserved: the sampler's launches share only the idxc list they write).
- *   Launches whose units are at most 6144 tokens long, with capacities of at least a sixth
- *   of that, take two kernels (selection, then the row gather "evict_copy"); other launches
- *   one ("evict_select" also gathers the rows).
+ *   (256 bytes, reserved, except for Poisson launches of fewer than 768 units longer than 16384
+ *   tokens: about 64 KB per unit, for which 256 bytes are still accepted, at a lower speed).
+ *   A call takes one kernel where the selection also gathers the rows, two where the gather is a
+ *   launch of its own ("evict_copy"), five for the long units above.
  *   Rows of Kc/Vc/pic/idxc beyond count[u] are left untouched.
  */
 ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint16_t *K,

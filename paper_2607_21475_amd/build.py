@@ -20,7 +20,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libebd.so")
 
-SOURCES = ["evict.hip", "attend.hip", "append.hip", "scores.hip", "finegrain.hip", "noalloc.hip",
+SOURCES = ["evict.hip", "evict_long.hip", "attend.hip", "append.hip", "scores.hip", "finegrain.hip", "noalloc.hip",
            "ebd_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -80,8 +80,23 @@ hipError_t timed(const char *name, hipStream_t s, F &&launch) {
   return hipSuccess;
 }
 
-// The sampler keeps no state between its two launches except the index list it writes.
+// The sampler's launches share only the index list they write, except where long units are selected
+// by segments (evict_long).
 constexpr size_t kEvictWorkspace = 256;
+
+// Whether units are long and few enough for the evict_long kernels: beyond what a work-group stages
+// in LDS, and fewer than keep every CU's work-groups busy with units of their own (the long
+// selection reads the scores five times and takes five launches).
+bool evict_long(const ebd_evict_params *p) {
+  return p->design == EBD_DESIGN_POISSON && p->max_rows > kEvictStageMax && p->max_rows <= kLongRowsMax &&
+         p->num_units < kEvictManyUnits;
+}
+
+size_t evict_workspace(const ebd_evict_params *p) {
+  return evict_long(p) && p->num_units > 0
+             ? (size_t)p->num_units * evict_long_unit_bytes(p->max_rows)
+             : kEvictWorkspace;
+}
 
 // Rows per split (a multiple of 16).  Unless the caller fixes it: one split per unit when there
 // are enough units for kSplitWaves waves, else units are cut into equal splits until there are;
@@ -325,7 +340,7 @@ size_t ebd_workspace_size(int32_t which, const void *params) {
   if (which == EBD_WS_EVICT) {
     const ebd_evict_params *p = static_cast<const ebd_evict_params *>(params);
     if (!valid_evict_params(p)) return 0;
-    return kEvictWorkspace;
+    return evict_workspace(p);
   }
   if (which == EBD_WS_ATTEND) {
     const ebd_attend_params *p = static_cast<const ebd_attend_params *>(params);
@@ -358,11 +373,12 @@ ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint1
   const ebd_status ds = check_device();
   if (ds != EBD_OK) return ds;
 
-  EvictLaunch L;
+  EvictLaunch L{};
   L.U = p->num_units;
   L.max_rows = p->max_rows;
   L.stage_rows = p->max_rows <= kEvictStageMax ? p->max_rows : 0;
   L.copy_blocks = (int32_t)((p->max_capacity + kCopyRows - 1) / kCopyRows);
+  L.gather = evict_select_gathers(L) ? 1 : 0;
   L.seq_off = p->seq_off;
   L.cap_off = p->cap_off;
   L.n_sink = p->n_sink;
@@ -387,9 +403,20 @@ ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint1
   L.pi_full = pi_full;
   L.status = status;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // a workspace of the smallest size still serves long units, by a work-group each
+  if (evict_long(p) && ws_bytes >= evict_workspace(p)) {
+    L.segs = (int32_t)((p->max_rows + kSegRows - 1) / kSegRows);
+    L.ws = static_cast<char *>(workspace);
+    L.ws_unit = (int64_t)evict_long_unit_bytes(p->max_rows);
+    if (timed("evict_select", s, [&] { return launch_evict_long_select(L, s); }) != hipSuccess)
+      return EBD_ERR_HIP;
+    if (timed("evict_copy", s, [&] { return launch_evict_long_write(L, s); }) != hipSuccess)
+      return EBD_ERR_HIP;
+    return EBD_OK;
+  }
   if (timed("evict_select", s, [&] { return launch_evict_select(L, s); }) != hipSuccess)
     return EBD_ERR_HIP;
-  if (L.copy_blocks > 0 && !evict_select_gathers(L) &&
+  if (L.copy_blocks > 0 && !L.gather &&
       timed("evict_copy", s, [&] { return launch_evict_copy(L, s); }) != hipSuccess)
     return EBD_ERR_HIP;
   return EBD_OK;

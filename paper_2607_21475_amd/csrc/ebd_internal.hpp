@@ -12,7 +12,11 @@ namespace ebd {
 constexpr int kHeadDim = 128;                // rows of K, V and q are 128 bf16
 constexpr int kEvictStageMax = 16384;        // scores staged in LDS (64 KB) up to this length
 constexpr int kSelectThreads = 512;          // evict_select (scores in LDS or streamed): eight waves per unit
+constexpr int kRegRowsMax = 6144;            // longest unit of evict_select_reg
 constexpr int kSelectRegThreads = 128;       // evict_select_reg: two waves per unit, <= 6144 tokens
+constexpr int kEvictManyUnits = 768;         // from here every CU has several units to select
+constexpr int kSegRows = 4096;               // tokens per work-group of the evict_long kernels
+constexpr int64_t kLongRowsMax = 1 << 21;    // longest unit of theirs (histogram counts and sums share 64 bits)
 constexpr int kCopyThreads = 256;            // evict_copy: 16 lanes per 256-byte row
 constexpr int kCopyRows = 128;               // retained rows per evict_copy work-group
 
@@ -65,7 +69,11 @@ struct EvictLaunch {
   int32_t U;
   int64_t max_rows;     // longest unit the launch was planned for
   int64_t stage_rows;   // LDS staging length of evict_select (0: scores streamed from memory)
+  int32_t gather;       // 1: evict_select also gathers the rows (no evict_copy launch)
   int32_t copy_blocks;  // evict_copy work-groups per unit = ceil(max capacity / kCopyRows)
+  int32_t segs;         // evict_long: segments per unit, workspace and its bytes per unit
+  char *ws;
+  int64_t ws_unit;
   const int64_t *seq_off;
   const int64_t *cap_off;
   int32_t n_sink, n_recent;
@@ -174,6 +182,9 @@ ebd_status attend_launch(const ebd_attend_params *p, const uint16_t *q, const ui
 hipError_t launch_evict_select(const EvictLaunch &L, hipStream_t s);
 hipError_t launch_evict_copy(const EvictLaunch &L, hipStream_t s);
 bool evict_select_gathers(const EvictLaunch &L);  // evict_select also gathers the rows (no copy launch)
+size_t evict_long_unit_bytes(int64_t max_rows);   // workspace of a unit of the evict_long kernels
+hipError_t launch_evict_long_select(const EvictLaunch &L, hipStream_t s);
+hipError_t launch_evict_long_write(const EvictLaunch &L, hipStream_t s);
 hipError_t launch_attend_split(const AttendLaunch &L, hipStream_t s);
 hipError_t launch_attend_finalize(const AttendLaunch &L, hipStream_t s);
 hipError_t launch_append_certain(const AppendLaunch &L, hipStream_t s);

@@ -2,11 +2,11 @@
 // Sec. 3.1: evicted rows are deleted, retained rows keep one stored pi each).
 //
 // Launches per call:
-//   evict_select_reg (units of at most 6144 tokens with a capacity of at least a sixth of their
-//                 length) one work-group of 2 waves per unit, the scores in registers, so that
+//   evict_select_reg (units of at most 6144 tokens of large launches, of at most 2048 of small ones)
+//                 one work-group of 2 waves per unit, the scores in registers, so that
 //                 every unit of a large batch is resident at once; the same steps as evict_select
 //                 below with one barrier per reduction or prefix; then evict_copy gathers the rows.
-//   evict_select  (every other launch) one work-group of 8 waves per unit, two per CU.  Stages the
+//   evict_select  (other launches) one work-group of 8 waves per unit, two per CU.  Stages the
 //                 unit's scores in LDS (up to 16384 tokens, protected positions marked by a
 //                 negative sentinel; longer units are re-read from memory), solves lambda with
 //                 sum_T clip(lambda s, eps, 1) = m by safeguarded Newton steps on the piecewise
@@ -16,9 +16,10 @@
 //                 (fixed-size systematic design), or the score threshold of a radix select (top-k
 //                 comparison design); ballot ranks plus a cross-wave prefix give the order in
 //                 which the stored pi and original position of every retained row are written,
-//                 plus the count and status bits.  The same work-group then gathers its unit's
-//                 retained K and V rows (the gathers of some units overlap the selection of
-//                 others; no second launch).
+//                 plus the count and status bits.  In large launches the same work-group then
+//                 gathers its unit's retained K and V rows (the gathers of some units overlap the
+//                 selection of others; no second launch).
+//   evict_long_*  (evict_long.hip: few units longer than LDS holds) every pass by segments.
 //   evict_copy    one work-group per (unit, block of retained rows): gathers the retained K and
 //                 V rows named by the index list (16 lanes x 16 B per 256-byte row, all loads of
 //                 a thread in flight together, non-temporal loads and stores: every byte is
@@ -26,25 +27,11 @@
 #include "ebd.h"
 #include "ebd_device.hpp"
 #include "ebd_internal.hpp"
+#include "evict_common.hpp"
 
 namespace ebd {
 
 namespace {
-
-// Non-finite and negative scores are read as 0 and flagged.
-__device__ __forceinline__ float clean_score(float s, uint32_t &bad) {
-  if (!(s >= 0.0f) || isinf(s)) {
-    bad = 1u;
-    return 0.0f;
-  }
-  return s == 0.0f ? 0.0f : s;  // -0 becomes +0 (the top-k keys are the score bits)
-}
-
-// pi of a position: 1 outside the tail, clip(lambda s, eps, 1) in it.  With lambda = +inf (no
-// eviction), lambda s is +inf for s > 0 (pi = 1) and NaN for s = 0, which fmaxf drops (pi = eps).
-__device__ __forceinline__ float token_pi(bool tail, float s, float lam, float eps) {
-  return tail ? fminf(fmaxf(lam * s, eps), 1.0f) : 1.0f;
-}
 
 // Block-wide reductions over the NW waves of evict_select.  `buf` alternates between calls so
 // that one barrier per call suffices.
@@ -139,59 +126,6 @@ __device__ __forceinline__ uint64_t pi_weight(float pi) {
   return t >= 4294967296.0f ? (1ull << 32) : (uint64_t)(uint32_t)ceilf(t);
 }
 
-// Tail statistics of a unit: |T|, positive scores, their sum, the largest score and the smallest
-// positive one.
-struct TailStats {
-  double n_tail, n_pos, s_sum;
-  float s_max, s_minp;
-};
-
-// lambda of eq. (2) with sum_T clip(lambda s, eps, 1) = m, plus the status bits of the boundary
-// cases.  `pass(lf, H, L, S, edges)` gives the unit's totals at lambda = lf: tail positions with
-// lf s >= 1 (H), with lf s <= eps (L), and the sum of the scores in between (S).
-// g(lambda) = H + eps L + lambda S is piecewise linear and nondecreasing: a Newton step on the
-// current piece is exact once the piece is right, and the bracket [lo, hi] with
-// g(lo) < m <= g(hi) guards every step (bisection when a step leaves it).
-//
-// The boundary cases (no tail, the literal lambda = m / sum s, the floor, no eviction): sets
-// lambda and the status bits and returns true; false when lambda is interior and needs the
-// iteration.
-__device__ inline bool lambda_boundary(const TailStats &T, double m, float eps, int pi_mode,
-                                       uint32_t &st, double &lam) {
-  if (T.n_tail == 0.0) {
-    lam = 0.0;
-    return true;
-  }
-  if (pi_mode == 1) {
-    if (m <= (double)eps * T.n_tail) st |= EBD_ST_BUDGET_FLOOR;
-    lam = (T.s_sum > 0.0 && m > 0.0) ? m / T.s_sum : 0.0;
-    return true;
-  }
-  if (m <= (double)eps * T.n_tail) {
-    st |= EBD_ST_BUDGET_FLOOR;
-    lam = 0.0;
-    return true;
-  }
-  if (m >= T.n_pos + (double)eps * (T.n_tail - T.n_pos)) {
-    st |= EBD_ST_NO_EVICTION;
-    lam = INFINITY;
-    return true;
-  }
-  return false;
-}
-
-// Where the scores of the evaluated piece lie: the smallest score of H, the largest and smallest
-// of the middle, the largest tail score of L.  A lambda whose fp32 products keep every token on
-// its side (monotone in s) gives a pass with exactly the same counts and sum.
-struct PieceEdges {
-  bool valid;  // false: not tracked by this pass
-  float h_min, m_max, m_min, l_max;
-  __device__ bool keeps(float lf, float eps) const {
-    return valid && lf * h_min >= 1.0f && lf * m_max < 1.0f && lf * m_min > eps &&
-           lf * l_max <= eps;
-  }
-};
-
 // Streamed units (scores re-read from memory on every pass) start the iteration from a lambda
 // solved on a histogram of their positive tail scores, gathered in the statistics pass: the bins
 // are the fp32 bit patterns shifted right by kHistShift (the exponent and five mantissa bits, 32
@@ -200,56 +134,8 @@ struct PieceEdges {
 // fewer passes over the scores than from the literal m / sum s (a CPU replay on Pareto scores:
 // 2.0 instead of 3.6); the lambda it ends on is the same exact solve of the piece it finds.
 // (Staged units gain nothing from it: their passes read LDS.)
-constexpr int kHistShift = 18;
-constexpr int kHistBins = 1 << (31 - kHistShift);
+// (kHistShift, kHistBins: evict_common.hpp.)
 
-// The iteration for an interior lambda within the bracket [lo, hi] (g(lo) < m <= g(hi)),
-// starting at cur.  pass(lf, H, L, S, edges) evaluates the piece at lf.  A Newton step that
-// stays on the evaluated piece is final: the next pass would find the same piece and stop there,
-// so a pass that reports the piece's edges saves that confirming pass.
-template <class Pass>
-__device__ double newton_lambda(double m, float eps, double lo, double hi, double cur,
-                                Pass &&pass) {
-  double pH = -1.0, pL = -1.0, pS = -1.0;
-  bool from_newton = false;
-  for (int it = 0; it < 96; ++it) {
-    const float lf = (float)cur;
-    double dH, dL, dS;
-    PieceEdges e;
-    pass(lf, dH, dL, dS, e);
-    if (from_newton && dH == pH && dL == pL && dS == pS) break;  // same piece: cur is exact
-    const double g = dH + (double)eps * dL + (double)lf * dS;
-    if (g < m) lo = (double)lf;
-    else hi = (double)lf;
-    if (g == m) break;
-    double nxt = dS > 0.0 ? (m - dH - (double)eps * dL) / dS : -1.0;
-    from_newton = (nxt > lo && nxt < hi);
-    if (!from_newton) nxt = 0.5 * (lo + hi);
-    if ((float)nxt == lf || hi - lo <= 1e-9 * hi) {
-      cur = from_newton ? nxt : cur;
-      break;
-    }
-    if (from_newton && e.keeps((float)nxt, eps)) {
-      cur = nxt;
-      break;
-    }
-    pH = dH;
-    pL = dL;
-    pS = dS;
-    cur = nxt;
-  }
-  return cur;
-}
-
-template <class Pass>
-__device__ double solve_lambda(const TailStats &T, double m, float eps, int pi_mode, uint32_t &st,
-                               Pass &&pass) {
-  double lam;
-  if (lambda_boundary(T, m, eps, pi_mode, st, lam)) return lam;
-  const double lo = (double)eps / (double)T.s_max;
-  const double hi = 1.0 / (double)T.s_minp;
-  return newton_lambda(m, eps, lo, hi, fmin(fmax(m / T.s_sum, lo), hi), pass);
-}
 
 // Top-k threshold: the k-th largest key among the tail keys (score bits, which order like the
 // non-negative cleaned scores), by radix select 8 bits per pass from the top over a histogram in
@@ -886,8 +772,8 @@ void evict_select_kernel(EvictLaunch L) {
   }
 
   // The unit's retained K and V rows, gathered by the same work-group from the index list it
-  // has just written (visible to it after the barrier).  Units of this kernel run in many
-  // generations, so one unit's gather overlaps other units' selection.
+  // has just written (visible to it after the barrier); otherwise evict_copy does.
+  if (!L.gather) return;
   __syncthreads();
   gather_rows<NT>(L, base, cbase, min(rank0, cap));
 }
@@ -1302,19 +1188,32 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
   }
 }
 
-// The eight-wave evict_select (which also gathers the rows) takes units longer than the register
-// kernel holds, and units whose capacity is under a sixth of their length: with few rows to
-// gather, its selection overlapping other units' gathers wins over the register kernel plus a
-// copy launch (measured on 6144-token units: 240 against 261 us at a 10% budget, 571 against
-// 561 us at 25%).
+// Whether evict_select's own work-groups gather their units' rows, or a copy launch follows.  With
+// many units the gathers of some overlap the latency-bound selection of others, which wins while
+// there are few rows to gather (a capacity under a sixth of the length) or the selection is long
+// (units past the register kernel): 1024 units of 16384 tokens, 10% / 25%: 348 / 862 us against
+// 403 / 882 us.  With fewer units than CUs most of the chip would watch the gather: 64 units of 16384
+// tokens, 25%: 137 against 90 us; 8 units of 8192 tokens: 56 against 29 us; in between the copy
+// launch wins from 25% on (256 units of 16384 tokens, 10 / 25 / 50%: 110 / 225 / 431 against 117 /
+// 221 / 400 us).
 bool evict_select_gathers(const EvictLaunch &L) {
-  return (L.max_rows + 511) / 512 > 12 || (int64_t)L.copy_blocks * kCopyRows * 6 < L.max_rows;
+  const bool few_rows = (int64_t)L.copy_blocks * kCopyRows * 6 < L.max_rows;
+  if (L.U < 256) return false;
+  if (L.U < kEvictManyUnits) return few_rows && L.max_rows <= kEvictStageMax;
+  return few_rows || L.max_rows > kRegRowsMax;
+}
+
+// The two-wave register kernel keeps every unit of a large launch resident at once; a small launch has
+// room for eight waves per unit, which are faster from 4096 tokens on (8 units of 6144 tokens: 23
+// against 28 us; at 2048 tokens 16 against 14 us).
+bool evict_select_in_regs(const EvictLaunch &L) {
+  return !L.gather && L.max_rows <= (L.U >= kEvictManyUnits ? kRegRowsMax : kRegRowsMax / 3);
 }
 
 hipError_t launch_evict_select(const EvictLaunch &L, hipStream_t s) {
   const dim3 grid((unsigned)L.U), reg(kSelectRegThreads);
   const int64_t g4 = (L.max_rows + 511) / 512;  // groups of 4 tokens per thread (two waves)
-  if (evict_select_gathers(L)) {
+  if (!evict_select_in_regs(L)) {
     // eight waves per unit, two units per CU: scores staged in LDS (up to 64 KB per unit) or,
     // for longer units, streamed from memory on every pass
     const size_t lds = L.stage_rows > 0 ? (size_t)((L.stage_rows + 3) / 4) * 16
