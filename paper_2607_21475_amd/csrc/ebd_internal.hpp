@@ -160,6 +160,7 @@ struct CertLaunch {
 };
 
 constexpr int64_t kMaxBlocks = 8192;  // blocks per unit of ebd_block_contributions (LDS bins)
+constexpr int kBlockWaves = 8;        // most waves of its work-groups
 
 size_t attend_workspace_bytes(int32_t U, int32_t nsplit, int32_t G, int32_t split_rows);
 size_t attend_fused_lds_bytes(int32_t split_rows, int gb);  // LDS of a split that also finalizes

@@ -2,12 +2,13 @@
 // "Finer grains"; App. "Experimental details": the fine-grained probe and the certificate
 // averaged over sampled heads and maximized over decode steps).
 //
-// block_contrib  one wave per (unit, block of <= 8 query heads), 16 retained rows per step on
-//                MFMA: kappa_hj = (1 - pi_j) (a_hj / (pi_j Nhat_h))^2 |v_j - yhat_h|^2, the
+// block_contrib  one work-group per (unit, block of <= 8 query heads), up to 8 waves that take the
+//                unit's tiles of 16 retained rows in turn, on MFMA: kappa_hj = (1 - pi_j) (a_hj / (pi_j Nhat_h))^2 |v_j - yhat_h|^2, the
 //                summand of Theorem 2, with a/(pi Nhat) = exp(scale q.k - ln pi - ln Nhat) from
-//                the certified attention's own outputs; summed over the heads and into the LDS
-//                bin of the row's original position / block_rows, then written (first head
-//                block) or added (later head blocks, launched in order) to the unit's blocks.
+//                the certified attention's own outputs; summed over the heads and into the wave's
+//                LDS bin of the row's original position / block_rows; the waves' bins are summed
+//                in order and written (first head block) or added (later head blocks, launched in
+//                order) to the unit's blocks.
 // cert_step      one work-group per sequence: the mean radius over the sampled (unit, query
 //                head) pairs, folded into a running maximum.
 #include "ebd.h"
@@ -45,7 +46,9 @@ __device__ __forceinline__ uint32_t bf16_top(float x) { return __float_as_uint(x
 
 }  // namespace
 
-// One wave per (unit, block of <= 8 query heads), 16 retained rows per step.  Two MFMA
+// One work-group per (unit, block of <= 8 query heads), 16 retained rows per wave and step.  With one
+// wave per unit a layer's probe (64 units of 1540 rows, G = 7) took 79 us on 64 of 1024 SIMDs, a
+// chain of 96 tiles each.  Two MFMA
 // contractions give, for every (head, row) pair, q_h.k_j (A = the heads' queries) and
 // yhat_h.v_j (A = yhat split exactly into three bf16 pieces, so that every product is exact and
 // only the fp32 sums round); with |v_j|^2 from the lane's own V dims, |v - yhat|^2 =
@@ -54,13 +57,15 @@ __device__ __forceinline__ uint32_t bf16_top(float x) { return __float_as_uint(x
 // for row 16t + c; the heads' terms are summed over the four row groups and added to the LDS bin
 // of the row's original position.
 template <int GB>
-__global__ __launch_bounds__(64, 2) void block_contrib_kernel(BlocksLaunch L, int h0) {
-  extern __shared__ float s_bin[];  // [nblocks], then |yhat|^2 [8], ln Nhat [8], yhat [GB][128]
-  float *s_yy = s_bin + L.nblocks;
+__global__ __launch_bounds__(64 * kBlockWaves) void block_contrib_kernel(BlocksLaunch L, int h0) {
+  extern __shared__ float s_all[];  // [waves][nblocks], then |yhat|^2 [8], ln Nhat [8], yhat [GB][128]
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nw = (int)(blockDim.x >> 6);
+  float *s_bin = s_all + (int64_t)wave * L.nblocks;  // this wave's bins
+  float *s_yy = s_all + (int64_t)nw * L.nblocks;
   float *s_l = s_yy + 8;
   float *s_y = s_l + 8;
   const int u = blockIdx.x;
-  const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int64_t cbase = L.cap_off[u];
   const int64_t cap = L.cap_off[u + 1] - cbase;
   const int cnt = (int)min(min((int64_t)L.count[u], cap), L.max_rows);
@@ -114,11 +119,11 @@ __global__ __launch_bounds__(64, 2) void block_contrib_kernel(BlocksLaunch L, in
   }
   yy += __shfl_xor(yy, 16);
   yy += __shfl_xor(yy, 32);
-  if (g == 0 && c < 8) {
+  if (wave == 0 && g == 0 && c < 8) {
     s_yy[c] = c < GB ? yy : 0.0f;
     s_l[c] = c < GB ? L.lse[uh0 + c] : 0.0f;
   }
-  for (int e = lane; e < GB * kHeadDim; e += 64) s_y[e] = L.y[uh0 * kHeadDim + e];
+  for (int e = threadIdx.x; e < GB * kHeadDim; e += blockDim.x) s_y[e] = L.y[uh0 * kHeadDim + e];
   __syncthreads();
 
   const float scale2 = L.scale * kLog2e;
@@ -152,8 +157,8 @@ __global__ __launch_bounds__(64, 2) void block_contrib_kernel(BlocksLaunch L, in
       }
     nv += __shfl_xor(nv, 16);
     nv += __shfl_xor(nv, 32);
-    const bool row_ok = 16 * t + c < cnt && T.p < 1.0f && T.ix >= 0 &&
-                        (int64_t)T.ix / L.block_rows < L.nblocks;
+    const uint32_t bin = (uint32_t)T.ix / (uint32_t)L.block_rows;
+    const bool row_ok = 16 * t + c < cnt && T.p < 1.0f && T.ix >= 0 && (int64_t)bin < L.nblocks;
     float d2[4];
     bool exact = false;
 #pragma unroll
@@ -198,25 +203,30 @@ __global__ __launch_bounds__(64, 2) void block_contrib_kernel(BlocksLaunch L, in
     }
     kap += __shfl_xor(kap, 16);
     kap += __shfl_xor(kap, 32);
-    if (g == 0 && row_ok) atomicAdd(&s_bin[T.ix / L.block_rows], kap);
+    if (g == 0 && row_ok) atomicAdd(&s_bin[bin], kap);
   };
+  // tiles wave, wave + nw, ...: three in registers, two in flight while one is computed
   BTile T0, T1, T2;
-  load_btile(T0, rK, rV, rP, rI, 0, g, c);
-  load_btile(T1, rK, rV, rP, rI, 1, g, c);
-  int t = 0;
-  for (; t + 3 <= ntile; t += 3) {
-    load_btile(T2, rK, rV, rP, rI, t + 2, g, c);
+  load_btile(T0, rK, rV, rP, rI, wave, g, c);
+  load_btile(T1, rK, rV, rP, rI, wave + nw, g, c);
+  int t = wave;
+  for (; t + 2 * nw < ntile; t += 3 * nw) {
+    load_btile(T2, rK, rV, rP, rI, t + 2 * nw, g, c);
     step(T0, t);
-    load_btile(T0, rK, rV, rP, rI, t + 3, g, c);
-    step(T1, t + 1);
-    load_btile(T1, rK, rV, rP, rI, t + 4, g, c);
-    step(T2, t + 2);
+    load_btile(T0, rK, rV, rP, rI, t + 3 * nw, g, c);
+    step(T1, t + nw);
+    load_btile(T1, rK, rV, rP, rI, t + 4 * nw, g, c);
+    step(T2, t + 2 * nw);
   }
   if (t < ntile) step(T0, t);
-  if (t + 1 < ntile) step(T1, t + 1);
+  if (t + nw < ntile) step(T1, t + nw);
   __syncthreads();
   float *out = L.blocks + (int64_t)u * L.nblocks;
-  for (int64_t b = lane; b < L.nblocks; b += 64) out[b] = (h0 == 0 ? 0.0f : out[b]) + s_bin[b];
+  for (int64_t b = threadIdx.x; b < L.nblocks; b += blockDim.x) {
+    float v = h0 == 0 ? 0.0f : out[b];
+    for (int w = 0; w < nw; ++w) v += s_all[w * L.nblocks + b];
+    out[b] = v;
+  }
 }
 
 constexpr int kCertThreads = 1024;
@@ -277,15 +287,25 @@ __global__ __launch_bounds__(kCertThreads) void cert_step_kernel(CertLaunch L) {
   }
 }
 
-size_t block_contrib_lds(int64_t nblocks, int gb) {
-  return (size_t)(nblocks + 16 + gb * kHeadDim) * sizeof(float);
+size_t block_contrib_lds(int64_t nblocks, int gb, int waves) {
+  return (size_t)(waves * nblocks + 16 + gb * kHeadDim) * sizeof(float);
+}
+
+// Waves per unit: enough for 2048 waves in the launch, at least two tiles each, and bins of at most
+// 64 KB together.
+int block_contrib_waves(const BlocksLaunch &L) {
+  int64_t w = 2048 / L.U;
+  w = w < (L.max_rows + 31) / 32 ? w : (L.max_rows + 31) / 32;
+  w = w < 16384 / L.nblocks ? w : 16384 / L.nblocks;
+  return (int)(w < 1 ? 1 : w > kBlockWaves ? kBlockWaves : w);
 }
 
 hipError_t launch_block_contrib(const BlocksLaunch &L, hipStream_t s) {
-  const dim3 grid((unsigned)L.U), block(64);
+  const int waves = block_contrib_waves(L);
+  const dim3 grid((unsigned)L.U), block(64 * waves);
   for (int h0 = 0; h0 < L.G; h0 += kHeadBlock) {
     const int gb = min(kHeadBlock, L.G - h0);
-    const size_t lds = block_contrib_lds(L.nblocks, gb);
+    const size_t lds = block_contrib_lds(L.nblocks, gb, waves);
     switch (gb) {
       case 1: hipLaunchKernelGGL(block_contrib_kernel<1>, grid, block, lds, s, L, h0); break;
       case 2: hipLaunchKernelGGL(block_contrib_kernel<2>, grid, block, lds, s, L, h0); break;
