@@ -190,19 +190,37 @@ __global__ __launch_bounds__(64, 2) void scores_accum_kernel(ScoresLaunch L) {
 
   Queries<NQB> Q;
   load_queries<NQB>(Q, L, u, n, g, c);
+  // The unit's normalisers: the four lanes of a query column take every fourth split, four loads
+  // in flight each (one after the other they took 20 of this pass's 28 us on 8 units of 32 splits),
+  // and their merges meet in a fixed order.
   float M[NQB], iZ[NQB];
 #pragma unroll
   for (int b = 0; b < NQB; ++b) {
     const int w = 16 * b + c;
     float mm = -INFINITY, zz = 0.0f;
-    if (w < L.W) {
-      const float2 *st = L.stats + (int64_t)u * L.nsplit * L.W + w;
-      for (int s = 0; s < nsp; ++s) {
-        const float2 v = st[(int64_t)s * L.W];
-        const float mn = fmaxf(mm, v.x);
-        zz = zz * exp2_rel(mm, mn) + v.y * exp2_rel(v.x, mn);
-        mm = mn;
+    const float2 *st = L.stats + (int64_t)u * L.nsplit * L.W + (w < L.W ? w : 0);
+    for (int s0 = 0; s0 < nsp; s0 += 16) {
+      float2 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int s = s0 + 4 * k + g;
+        v[k] = st[(int64_t)min(s, nsp - 1) * L.W];
+        if (s >= nsp || w >= L.W) v[k] = make_float2(-INFINITY, 0.0f);
       }
+      float mn = mm;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mn = fmaxf(mn, v[k].x);
+      zz *= exp2_rel(mm, mn);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) zz += v[k].y * exp2_rel(v[k].x, mn);
+      mm = mn;
+    }
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float mo = __shfl_xor(mm, o), zo = __shfl_xor(zz, o);
+      const float mn = fmaxf(mm, mo);
+      zz = zz * exp2_rel(mm, mn) + zo * exp2_rel(mo, mn);
+      mm = mn;
     }
     M[b] = mm == -INFINITY ? 0.0f : mm;
     iZ[b] = zz > 0.0f ? 1.0f / zz : 0.0f;
