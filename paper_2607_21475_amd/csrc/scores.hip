@@ -251,20 +251,24 @@ __global__ __launch_bounds__(64, 2) void scores_accum_kernel(ScoresLaunch L) {
                                             c < 4 ? (uint32_t)(rrel + c) * 4u : 0xfffffff0u, 0, 0);
     }
   };
+  // From the last tile to the first: what pass 1 read last is what the last-level cache still holds
+  // when K is larger than it (both passes, 256 units of 16384 tokens: 406 -> 388 us; 128: 209 -> 196
+  // us; 16: 31.9 -> 27.5 us).  Tiles before the first are out of the buffers' range (their offsets
+  // wrap past it) and read as zero.
   KTile T0, T1, T2;
-  load_ktile<ACC>(T0, rK, rS, 0, g, c);
-  load_ktile<ACC>(T1, rK, rS, 1, g, c);
-  int t = 0;
-  for (; t + 3 <= ntile; t += 3) {
-    load_ktile<ACC>(T2, rK, rS, t + 2, g, c);
+  load_ktile<ACC>(T0, rK, rS, ntile - 1, g, c);
+  load_ktile<ACC>(T1, rK, rS, ntile - 2, g, c);
+  int t = ntile - 1;
+  for (; t >= 2; t -= 3) {
+    load_ktile<ACC>(T2, rK, rS, t - 2, g, c);
     step(T0, t);
-    load_ktile<ACC>(T0, rK, rS, t + 3, g, c);
-    step(T1, t + 1);
-    load_ktile<ACC>(T1, rK, rS, t + 4, g, c);
-    step(T2, t + 2);
+    load_ktile<ACC>(T0, rK, rS, t - 3, g, c);
+    step(T1, t - 1);
+    load_ktile<ACC>(T1, rK, rS, t - 4, g, c);
+    step(T2, t - 2);
   }
-  if (t < ntile) step(T0, t);
-  if (t + 1 < ntile) step(T1, t + 1);
+  if (t >= 0) step(T0, t);
+  if (t >= 1) step(T1, t - 1);
 }
 
 size_t scores_workspace_bytes(int32_t U, int32_t nsplit, int32_t W) {
