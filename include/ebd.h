@@ -129,7 +129,8 @@ typedef struct ebd_evict_params {
  *   (256 bytes, reserved, except for Poisson launches of fewer than 768 units longer than 16384
  *   tokens: about 64 KB per unit, for which 256 bytes are still accepted, at a lower speed).
  *   A call takes one kernel where the selection also gathers the rows, two where the gather is a
- *   launch of its own ("evict_copy"), five for the long units above.
+ *   launch of its own ("evict_copy") or a large unit's later rows are (timed with "evict_select"), five
+ *   for the long units above.
  *   Rows of Kc/Vc/pic/idxc beyond count[u] are left untouched.
  */
 ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint16_t *K,

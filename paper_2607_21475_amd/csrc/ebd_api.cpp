@@ -378,7 +378,7 @@ ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint1
   L.max_rows = p->max_rows;
   L.stage_rows = p->max_rows <= kEvictStageMax ? p->max_rows : 0;
   L.copy_blocks = (int32_t)((p->max_capacity + kCopyRows - 1) / kCopyRows);
-  L.gather = evict_select_gathers(L) ? 1 : 0;
+  L.gather = evict_gather_rows(L);
   L.seq_off = p->seq_off;
   L.cap_off = p->cap_off;
   L.n_sink = p->n_sink;
@@ -414,9 +414,14 @@ ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint1
       return EBD_ERR_HIP;
     return EBD_OK;
   }
-  if (timed("evict_select", s, [&] { return launch_evict_select(L, s); }) != hipSuccess)
+  // the rows that a gathering selection leaves to evict_copy count as its own launch's
+  const bool rest = L.gather > 0 && L.copy_blocks > L.gather / kCopyRows;
+  if (timed("evict_select", s, [&] {
+        const hipError_t e = launch_evict_select(L, s);
+        return e == hipSuccess && rest ? launch_evict_copy(L, s) : e;
+      }) != hipSuccess)
     return EBD_ERR_HIP;
-  if (L.copy_blocks > 0 && !L.gather &&
+  if (L.copy_blocks > 0 && L.gather == 0 &&
       timed("evict_copy", s, [&] { return launch_evict_copy(L, s); }) != hipSuccess)
     return EBD_ERR_HIP;
   return EBD_OK;

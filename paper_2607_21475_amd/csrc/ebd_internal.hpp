@@ -15,6 +15,9 @@ constexpr int kSelectThreads = 512;          // evict_select (scores in LDS or s
 constexpr int kRegRowsMax = 6144;            // longest unit of evict_select_reg
 constexpr int kSelectRegThreads = 128;       // evict_select_reg: two waves per unit, <= 6144 tokens
 constexpr int kEvictManyUnits = 768;         // from here every CU has several units to select
+constexpr int kGatherMinRows = 1024;         // rows of a unit that its own work-group gathers (multiples
+constexpr int kGatherMaxRows = 4096;         // ... of kCopyRows)
+constexpr int kGatherFewRows = 512;          // units of small launches gathered without a copy launch
 constexpr int kSegRows = 4096;               // tokens per work-group of the evict_long kernels
 constexpr int64_t kLongRowsMax = 1 << 21;    // longest unit of theirs (histogram counts and sums share 64 bits)
 constexpr int kCopyThreads = 256;            // evict_copy: 16 lanes per 256-byte row
@@ -69,7 +72,7 @@ struct EvictLaunch {
   int32_t U;
   int64_t max_rows;     // longest unit the launch was planned for
   int64_t stage_rows;   // LDS staging length of evict_select (0: scores streamed from memory)
-  int32_t gather;       // 1: evict_select also gathers the rows (no evict_copy launch)
+  int32_t gather;       // rows of each unit that evict_select gathers itself (evict_copy takes the rest)
   int32_t copy_blocks;  // evict_copy work-groups per unit = ceil(max capacity / kCopyRows)
   int32_t segs;         // evict_long: segments per unit, workspace and its bytes per unit
   char *ws;
@@ -182,7 +185,7 @@ ebd_status attend_launch(const ebd_attend_params *p, const uint16_t *q, const ui
 
 hipError_t launch_evict_select(const EvictLaunch &L, hipStream_t s);
 hipError_t launch_evict_copy(const EvictLaunch &L, hipStream_t s);
-bool evict_select_gathers(const EvictLaunch &L);  // evict_select also gathers the rows (no copy launch)
+int32_t evict_gather_rows(const EvictLaunch &L);  // rows of each unit that evict_select gathers itself
 size_t evict_long_unit_bytes(int64_t max_rows);   // workspace of a unit of the evict_long kernels
 hipError_t launch_evict_long_select(const EvictLaunch &L, hipStream_t s);
 hipError_t launch_evict_long_write(const EvictLaunch &L, hipStream_t s);

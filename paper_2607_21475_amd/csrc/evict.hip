@@ -17,8 +17,8 @@
 //                 comparison design); ballot ranks plus a cross-wave prefix give the order in
 //                 which the stored pi and original position of every retained row are written,
 //                 plus the count and status bits.  In large launches the same work-group then
-//                 gathers its unit's retained K and V rows (the gathers of some units overlap the
-//                 selection of others; no second launch).
+//                 gathers its unit's first retained K and V rows (the gathers of some units overlap
+//                 the selection of others), and evict_copy those past evict_gather_rows.
 //   evict_long_*  (evict_long.hip: few units longer than LDS holds) every pass by segments.
 //   evict_copy    one work-group per (unit, block of retained rows): gathers the retained K and
 //                 V rows named by the index list (16 lanes x 16 B per 256-byte row, all loads of
@@ -771,11 +771,11 @@ void evict_select_kernel(EvictLaunch L) {
     if (L.lambda_out) L.lambda_out[u] = lamf;
   }
 
-  // The unit's retained K and V rows, gathered by the same work-group from the index list it
-  // has just written (visible to it after the barrier); otherwise evict_copy does.
+  // The unit's first retained K and V rows, gathered by the same work-group from the index list it
+  // has just written (visible to it after the barrier); evict_copy takes the others.
   if (!L.gather) return;
   __syncthreads();
-  gather_rows<NT>(L, base, cbase, min(rank0, cap));
+  gather_rows<NT>(L, base, cbase, min(min(rank0, cap), (int64_t)L.gather));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1145,12 +1145,13 @@ void evict_select_reg_kernel(EvictLaunch L) {
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L) {
   const int64_t bid = blockIdx.x;
-  const int blk = (int)(bid % L.copy_blocks);
-  const int u = (int)(bid / L.copy_blocks);
+  const int rest = L.copy_blocks - L.gather / kCopyRows;  // the blocks evict_select has not gathered
+  const int blk = (int)(bid % rest);
+  const int u = (int)(bid / rest);
   const int64_t cbase = L.cap_off[u];
   const int64_t cap = L.cap_off[u + 1] - cbase;
   const int64_t nkeep = min((int64_t)L.count[u], cap);
-  const int64_t r0 = (int64_t)blk * kCopyRows;
+  const int64_t r0 = (int64_t)L.gather + (int64_t)blk * kCopyRows;
   if (r0 >= nkeep || (L.seq_off[u + 1] - L.seq_off[u]) > L.max_rows) return;
   const int64_t base = L.seq_off[u];
   const int sub = threadIdx.x & 15;
@@ -1193,14 +1194,31 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
 // there are few rows to gather (a capacity under a sixth of the length) or the selection is long
 // (units past the register kernel): 1024 units of 16384 tokens, 10% / 25%: 348 / 862 us against
 // 403 / 882 us.  With fewer units than CUs most of the chip would watch the gather: 64 units of 16384
-// tokens, 25%: 137 against 90 us; 8 units of 8192 tokens: 56 against 29 us; in between the copy
+// tokens, 25%: 137 against 90 us; 8 units of 8192 tokens: 56 against 29 us (up to 512 rows the launch
+// costs more than it saves: 181 units of up to 325 rows 26.7 against 23.1 us); in between the copy
 // launch wins from 25% on (256 units of 16384 tokens, 10 / 25 / 50%: 110 / 225 / 431 against 117 /
 // 221 / 400 us).
-bool evict_select_gathers(const EvictLaunch &L) {
-  const bool few_rows = (int64_t)L.copy_blocks * kCopyRows * 6 < L.max_rows;
-  if (L.U < 256) return false;
-  if (L.U < kEvictManyUnits) return few_rows && L.max_rows <= kEvictStageMax;
-  return few_rows || L.max_rows > kRegRowsMax;
+//
+// A gathering work-group takes evict_gather_rows of its unit's rows and evict_copy, which fills the
+// chip whatever the units' sizes, the others: where lengths and budgets differ, a unit selected late
+// with eight times the mean's rows was gathered by one CU while the others had finished.  A sixteenth
+// of the longest unit, 1024 to 4096 rows, is enough to cover the others' selection: 1008 units of 2048
+// to 16384 tokens at 5 to 50%: all rows 500, first 4096 / 2048 / 1024 / 512 rows 431 / 388 / 370 /
+// 375 us; 800 units of up to 131072 tokens: all 3618, first 16384 / 8192 / 4096 / 1024 rows 2906 / 2724 /
+// 2713 / 2851 us; equal units of 16384 tokens, 25%: 740 against 743 us.  Up to twice that many rows a
+// unit is gathered whole (2048 units of 16384 tokens, 10%: 651 us, 668 with a launch for the rest).
+int32_t evict_gather_rows(const EvictLaunch &L) {
+  const int64_t capacity = (int64_t)L.copy_blocks * kCopyRows;
+  const bool few_rows = capacity * 6 < L.max_rows;
+  if (L.U < 256) return few_rows && capacity <= kGatherFewRows && L.max_rows > kRegRowsMax / 3 ? (int32_t)capacity : 0;
+  if (L.U < kEvictManyUnits) {
+    if (!few_rows || L.max_rows > kEvictStageMax) return 0;
+  } else if (!few_rows && L.max_rows <= kRegRowsMax) {
+    return 0;
+  }
+  const int64_t share = L.max_rows / 16 / kCopyRows * kCopyRows;
+  const int64_t first = share < kGatherMinRows ? kGatherMinRows : share > kGatherMaxRows ? kGatherMaxRows : share;
+  return (int32_t)(capacity <= 2 * first ? 2 * first : first);
 }
 
 // The two-wave register kernel keeps every unit of a large launch resident at once; a small launch has
@@ -1227,7 +1245,7 @@ hipError_t launch_evict_select(const EvictLaunch &L, hipStream_t s) {
 }
 
 hipError_t launch_evict_copy(const EvictLaunch &L, hipStream_t s) {
-  const dim3 grid((unsigned)((int64_t)L.U * L.copy_blocks)), block(kCopyThreads);
+  const dim3 grid((unsigned)((int64_t)L.U * (L.copy_blocks - L.gather / kCopyRows))), block(kCopyThreads);
   hipLaunchKernelGGL(evict_copy_kernel, grid, block, 0, s, L);
   return hipGetLastError();
 }
