@@ -439,6 +439,18 @@ struct Row16 {
   }
 };
 
+// Pivot rows that a lane group of 8 reads at a time (one after the other they took most of the
+// combination's 4.5 us).
+constexpr int kPivBatch = 4;
+
+// Sum over a lane group of 8; every lane of the group receives it.
+__device__ __forceinline__ float sum_group8(float x) {
+  x += dpp_f<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += dpp_f<0x4E>(x);   // quad_perm [2,3,0,1]
+  x += dpp_f<0x141>(x);  // row_half_mirror: the group's other quad
+  return x;
+}
+
 // Before the finalize of a unit that one wave read whole: per head, the list entry with the largest
 // logit becomes the pivot (kept in the head's table), the running max is raised to its logit if
 // needed (the sums rescaled), and every other entry is added back into l, o, C0, Cv, C2 exactly.
@@ -583,12 +595,9 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
         yo[q] = oh[q];
       }
     }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-      yy += __shfl_xor(yy, o);
-      ycv += __shfl_xor(ycv, o);
-      dd += __shfl_xor(dd, o);
-    }
+    yy = sum_group8(yy);
+    ycv = sum_group8(ycv);
+    dd = sum_group8(dd);
     if (h < GB && j == 0) {
       float *hs = F.hs + h * kHs;
       const bool piv = hs[kHsPl] > -INFINITY;
@@ -627,23 +636,27 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
       const int s = GB > 1 ? 0 : s0 + gi;
       const float *pl = P.at(min(s, nsp - 1), hh);
       const int n = (GB > 1 ? gi < GB : s < nsp) ? __float_as_int(pl[0]) : 0;
-      for (int e = 0; e < kPivMax; ++e) {
-        if (!__any(e < n)) break;
-        const bool have = e < n && s * kPivMax + e != pk;
-        Row16 v;
-        v.load(L.Vc, cbase, have ? __float_as_int(pl[1 + 3 * e]) : 0, j);
-        float d2 = 0.0f;
+      for (int e0 = 0; e0 < kPivMax; e0 += kPivBatch) {
+        if (!__any(e0 < n)) break;
+        Row16 v[kPivBatch];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const float a = bf16_lo(v.w[t]) - yh[2 * t], b = bf16_hi(v.w[t]) - yh[2 * t + 1];
-          d2 = fmaf(a, a, d2);
-          d2 = fmaf(b, b, d2);
+        for (int k = 0; k < kPivBatch; ++k)
+          v[k].load(L.Vc, cbase, e0 + k < n ? __float_as_int(pl[1 + 3 * (e0 + k)]) : 0, j);
+#pragma unroll
+        for (int k = 0; k < kPivBatch; ++k) {
+          const int e = e0 + k;
+          const bool have = e < n && s * kPivMax + e != pk;
+          float d2 = 0.0f;
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const float a = bf16_lo(v[k].w[t]) - yh[2 * t], b = bf16_hi(v[k].w[t]) - yh[2 * t + 1];
+            d2 = fmaf(a, a, d2);
+            d2 = fmaf(b, b, d2);
+          }
+          d2 = sum_group8(d2);
+          if (have)
+            bmax = fmaxf(bmax, sqrtf(1.0f - pl[3 + 3 * e]) * fast_exp2(pl[2 + 3 * e] - M) * sqrtf(d2) * il);
         }
-        d2 += __shfl_xor(d2, 1);
-        d2 += __shfl_xor(d2, 2);
-        d2 += __shfl_xor(d2, 4);
-        if (have)
-          bmax = fmaxf(bmax, sqrtf(1.0f - pl[3 + 3 * e]) * fast_exp2(pl[2 + 3 * e] - M) * sqrtf(d2) * il);
       }
     }
     if (GB == 1) {
@@ -703,7 +716,11 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
     return C.base + s * C.sstride + k * C.kstride + h * C.hstride;
   };
   // One lane per block: candidate j's bound is g_j F with F = f (Vmax + |yhat|) / l, so the
-  // block's largest g decides; per head, the largest bound (and its candidate) goes to F.best.
+  // block's largest g decides; per head, the largest bound (and its candidate, the last of equal
+  // ones) goes to F.best: by LDS atomics for several heads, by lane exchanges for one head, whose
+  // blocks' atomics would all meet at one address (180 blocks: 10 us).
+  float ub1 = 0.0f;
+  int e1 = -1;
   for (int x0 = 0; x0 < nx; x0 += 64) {
     int h;
     const float *blk = block_at(x0 + lane, h);
@@ -725,10 +742,21 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
       }
       const float *hs = F.hs + h * kHs;
       const float ub = scale_of(blk[kChM], hs[kHsM]) * gmax / hs[kHsL] * (blk[kChVmax] + hs[kHsYn]);
-      if (ub > 0.0f)
+      if (GB == 1) {
+        if (ub > 0.0f && ub >= ub1) {  // a lane's blocks ascend
+          ub1 = ub;
+          e1 = (x0 + lane) * kCand + jmax;
+        }
+      } else if (ub > 0.0f)
         atomicMax(&F.best[h], ((unsigned long long)__float_as_uint(ub) << 32) |
                                   (unsigned)((x0 + lane) * kCand + jmax));
     }
+  }
+  if (GB == 1) {
+    const float top = wave_max(ub1);
+    const int e = wave_reduce(ub1 == top ? e1 : -1, [](int a, int b) { return a > b ? a : b; });
+    if (lane == 0 && e >= 0)
+      F.best[0] = ((unsigned long long)__float_as_uint(top) << 32) | (unsigned)e;
   }
   wave_sync();
 
@@ -758,8 +786,7 @@ __device__ __forceinline__ void finalize_block(const AttendLaunch &L, int u, int
         }
       }
     }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) d2 += __shfl_xor(d2, o);
+    d2 = sum_group8(d2);
     if (have && j == 0) F.hs[h * kHs + kHsLb] = fmaxf(F.hs[h * kHs + kHsLb], fg * sqrtf(d2));
   }
   wave_sync();
@@ -1172,14 +1199,10 @@ __device__ __forceinline__ void combine_head(const AttendLaunch &L, int64_t cbas
     }
   }
   mm = wave_max(mm);
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const float ol = __shfl_xor(bl, o);
-    const int ok = __shfl_xor(bk, o);
-    if (ol > bl || (ol == bl && ok < bk)) {
-      bl = ol;
-      bk = ok;
-    }
+  {  // the largest logit, of equal ones the first entry
+    const float best = wave_max(bl);
+    bk = wave_min(bl == best ? bk : 0x7fffffff);
+    bl = best;
   }
   const float M1 = fmaxf(mm, bl);
 
@@ -1210,53 +1233,55 @@ __device__ __forceinline__ void combine_head(const AttendLaunch &L, int64_t cbas
         c16[4 * k + t] = fmaf(f2, c[t], c16[4 * k + t]);
       }
     }
-    for (int e = 0; e < kPivMax; ++e) {
-      if (!__any(e < n)) break;
-      const bool have = e < n && s * kPivMax + e != bk;
-      const int row = have ? __float_as_int(pl[1 + 3 * e]) : 0;
-      Row16 v;
-      v.load(L.Vc, cbase, row, j);
-      const float w = have ? fast_exp2(pl[2 + 3 * e] - M1) : 0.0f;
-      const float cc = have ? (1.0f - pl[3 + 3 * e]) * w * w : 0.0f;
-      float nv = 0.0f;
+    // the list entries, kPivBatch value rows in flight at a time
+    for (int e0 = 0; e0 < kPivMax; e0 += kPivBatch) {
+      if (!__any(e0 < n)) break;
+      Row16 v[kPivBatch];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float x0 = bf16_lo(v.w[t]), x1 = bf16_hi(v.w[t]);
-        o16[2 * t] = fmaf(w, x0, o16[2 * t]);
-        o16[2 * t + 1] = fmaf(w, x1, o16[2 * t + 1]);
-        c16[2 * t] = fmaf(cc, x0, c16[2 * t]);
-        c16[2 * t + 1] = fmaf(cc, x1, c16[2 * t + 1]);
-        nv = fmaf(x0, x0, nv);
-        nv = fmaf(x1, x1, nv);
-      }
-      nv += __shfl_xor(nv, 1);
-      nv += __shfl_xor(nv, 2);
-      nv += __shfl_xor(nv, 4);
-      la += w;
-      c0a += cc;
-      c2a = fmaf(cc, nv, c2a);
-      if (s_extra && have && j == 0 && cc > 0.0f) {
-        const int x = s * kPivMax + e;
-        float *blk = s_extra + (x / kCand) * kChunkFloats;
-        blk[kChG + x % kCand] = fast_sqrt(cc);
-        reinterpret_cast<uint16_t *>(blk + kChI)[x % kCand] = (uint16_t)(row - row_first);
-        atomicMax(reinterpret_cast<unsigned *>(blk + kChVmax), __float_as_uint(fast_sqrt(nv) * 1.000001f));
-        blk[kChM] = M1;
+      for (int k = 0; k < kPivBatch; ++k)
+        v[k].load(L.Vc, cbase, e0 + k < n ? __float_as_int(pl[1 + 3 * (e0 + k)]) : 0, j);
+#pragma unroll
+      for (int k = 0; k < kPivBatch; ++k) {
+        const int e = e0 + k;
+        const bool have = e < n && s * kPivMax + e != bk;
+        const float w = have ? fast_exp2(pl[2 + 3 * e] - M1) : 0.0f;
+        const float cc = have ? (1.0f - pl[3 + 3 * e]) * w * w : 0.0f;
+        float nv = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const float x0 = bf16_lo(v[k].w[t]), x1 = bf16_hi(v[k].w[t]);
+          o16[2 * t] = fmaf(w, x0, o16[2 * t]);
+          o16[2 * t + 1] = fmaf(w, x1, o16[2 * t + 1]);
+          c16[2 * t] = fmaf(cc, x0, c16[2 * t]);
+          c16[2 * t + 1] = fmaf(cc, x1, c16[2 * t + 1]);
+          nv = fmaf(x0, x0, nv);
+          nv = fmaf(x1, x1, nv);
+        }
+        nv = sum_group8(nv);
+        la += w;
+        c0a += cc;
+        c2a = fmaf(cc, nv, c2a);
+        if (s_extra && have && j == 0 && cc > 0.0f) {
+          const int x = s * kPivMax + e;
+          float *blk = s_extra + (x / kCand) * kChunkFloats;
+          blk[kChG + x % kCand] = fast_sqrt(cc);
+          reinterpret_cast<uint16_t *>(blk + kChI)[x % kCand] =
+              (uint16_t)(__float_as_int(pl[1 + 3 * e]) - row_first);
+          atomicMax(reinterpret_cast<unsigned *>(blk + kChVmax), __float_as_uint(fast_sqrt(nv) * 1.000001f));
+          blk[kChM] = M1;
+        }
       }
     }
   }
   // the eight groups' totals, the same in every lane of a column of lanes
 #pragma unroll
-  for (int o = 8; o < 64; o <<= 1) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      o16[t] += __shfl_xor(o16[t], o);
-      c16[t] += __shfl_xor(c16[t], o);
-    }
-    la += __shfl_xor(la, o);
-    c0a += __shfl_xor(c0a, o);
-    c2a += __shfl_xor(c2a, o);
+  for (int t = 0; t < 16; ++t) {
+    o16[t] = add_xor32(add_xor16(add_xor8(o16[t])));
+    c16[t] = add_xor32(add_xor16(add_xor8(c16[t])));
   }
+  la = add_xor32(add_xor16(add_xor8(la)));
+  c0a = add_xor32(add_xor16(add_xor8(c0a)));
+  c2a = add_xor32(add_xor16(add_xor8(c2a)));
   wave_sync();  // F may lie over the records' sums: they are read
   if (gi == 0) {
     float4 *op = reinterpret_cast<float4 *>(F.o + 16 * j);
@@ -1517,11 +1542,14 @@ __global__ __launch_bounds__(SHARED ? 64 * kUnitWaves : 64, 2) void attend_split
 }
 
 // attend_finalize: one wave per (unit, head) when units are cut into several records: combined
-// with a lane group per record, then finalized like a unit whose sums are in LDS, the candidate
-// blocks read from the records (a lane per block, whole blocks as float4).  With one wave for a
-// unit's whole head block and the records' pivots walked one after another it took 32 us for 256
-// units of 6 records and 146 us for 8 units of 52.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// with a lane group per record, then finalized like a unit whose sums are in LDS (a lane per
+// candidate block, whole blocks as float4).  With one wave for a unit's whole head block and the
+// records' pivots walked one after another it took 32 us for 256 units of 6 records and 146 us for 8
+// units of 52.  What bounds it is a chain of dependent reads, a dozen of them of the records, which
+// other XCDs wrote: STAGED work-groups of four waves copy the head's records into LDS first, all
+// loads in flight at once, and one wave goes on from there.
+template <bool STAGED>
+__global__ __launch_bounds__(STAGED ? 256 : 64) __attribute__((amdgpu_waves_per_eu(4)))
 void attend_finalize_kernel(AttendLaunch L) {
   extern __shared__ float s_fin[];
   const int u = blockIdx.x / L.G, h = blockIdx.x % L.G;
@@ -1533,12 +1561,37 @@ void attend_finalize_kernel(AttendLaunch L) {
   const int nsp = (cnt + r * L.wpg - 1) / (r * L.wpg);
   const float *rec0 = L.part + ((int64_t)u * L.nsplit * L.G + h) * L.rec;
   const int64_t sstride = (int64_t)L.G * L.rec;
-  const FinLds<1> F(s_fin);
-  combine_head(L, cbase, nsp, rec0, sstride, F, nullptr, 0);
   const BlockGeo B{r, L.wpg, L.nchunk, L.wpg * L.nchunk + (L.wpg > 1 ? 2 : 0)};
-  const CandSrc C{rec0 + kRecChunks, sstride, kChunkFloats, 0};
-  const PivSrc P{rec0 + kRecPiv, sstride, 0};
-  finalize_block<1>(L, u, h, cnt, cbase, nsp, B, C, P, F);
+  if constexpr (STAGED) {
+    float *s_rec = s_fin + (FinLds<1>::bytes() + 15) / 16 * 4;
+    const int q = L.rec / 4, total = nsp * q;  // records are whole float4 words
+    const float4 *src = reinterpret_cast<const float4 *>(rec0);
+    constexpr int kIn = 16;
+    for (int e0 = threadIdx.x; e0 < total; e0 += 256 * kIn) {
+      float4 v[kIn];
+#pragma unroll
+      for (int k = 0; k < kIn; ++k) {
+        const int e = min(e0 + 256 * k, total - 1), s = e / q;
+        v[k] = src[s * (sstride / 4) + (e - s * q)];
+      }
+#pragma unroll
+      for (int k = 0; k < kIn; ++k)
+        if (e0 + 256 * k < total) reinterpret_cast<float4 *>(s_rec)[e0 + 256 * k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const FinLds<1> F(s_fin);
+    combine_head(L, cbase, nsp, s_rec, L.rec, F, nullptr, 0);
+    const CandSrc C{s_rec + kRecChunks, L.rec, kChunkFloats, 0};
+    const PivSrc P{s_rec + kRecPiv, L.rec, 0};
+    finalize_block<1>(L, u, h, cnt, cbase, nsp, B, C, P, F);
+  } else {
+    const FinLds<1> F(s_fin);
+    combine_head(L, cbase, nsp, rec0, sstride, F, nullptr, 0);
+    const CandSrc C{rec0 + kRecChunks, sstride, kChunkFloats, 0};
+    const PivSrc P{rec0 + kRecPiv, sstride, 0};
+    finalize_block<1>(L, u, h, cnt, cbase, nsp, B, C, P, F);
+  }
 }
 
 size_t attend_workspace_bytes(int32_t U, int32_t nsplit, int32_t G, int32_t split_rows) {
@@ -1610,8 +1663,14 @@ hipError_t launch_attend_split(const AttendLaunch &L, hipStream_t s) {
 }
 
 hipError_t launch_attend_finalize(const AttendLaunch &L, hipStream_t s) {
-  hipLaunchKernelGGL(attend_finalize_kernel, dim3((unsigned)((int64_t)L.U * L.G)), dim3(64),
-                     FinLds<1>::bytes(), s, L);
+  const dim3 grid((unsigned)((int64_t)L.U * L.G));
+  const size_t own = (FinLds<1>::bytes() + 15) / 16 * 16;
+  const size_t staged = own + (size_t)L.nsplit * (size_t)L.rec * sizeof(float);
+  // staged work-groups have four waves and run two per CU: beyond 512 of them a wave each is quicker
+  if ((int64_t)L.U * L.G <= 512 && staged <= kUnitLdsMax && L.rec % 4 == 0)
+    hipLaunchKernelGGL(attend_finalize_kernel<true>, grid, dim3(256), staged, s, L);
+  else
+    hipLaunchKernelGGL(attend_finalize_kernel<false>, grid, dim3(64), FinLds<1>::bytes(), s, L);
   return hipGetLastError();
 }
 

@@ -151,10 +151,19 @@ int64_t part_record_floats(int32_t rows, int32_t wpg) {
 //  * Many units (one split each): a wave per unit.
 //  * Otherwise a work-group of up to eight waves shares a unit, as many as keep 2048 waves resident
 //    (8 waves up to 256 units, 4 up to 512, 2 up to 1024 and above).  One work-group per unit
-//    needs no record and no second launch, and its waves read 16 rows in about 0.8 us, so it is kept
-//    to 3584 rows (28 tiles per wave) and for 256 units or more, where the memory is busy anyway;
-//    longer units of smaller launches are cut into parts until 256 work-groups run, at least 96
-//    rows per wave.
+//    needs no record and no second launch, but its waves read 16 rows in about 1.3 us, so launches of
+//    fewer than 256 units cut theirs into parts until 256 work-groups run, at least 96 rows per
+//    wave: 8 units of 2070 rows, G = 4: 44.6 us whole, 35.3 us in parts; 64 ragged units of up to 3000
+//    rows, G = 7: 57.6 and 40.1 us; 128 units of 2140 rows: 49.6 and 46.6 us; one part (1025 rows): 32.4 us.
+//    Short units are quicker by a wave each (the estimate below), above all where a work-group has
+//    fewer waves than heads: 755 units of up to 400 rows, G = 8: 66 us shared, 35 us by a wave each;
+//    527 of up to 340 rows, G = 3: 42 and 31 us; 1286 of up to 960 rows, G = 6: 132 and 90 us (from 2560 rows on two
+//    waves win there: 1124 ragged units of up to 3600 rows 275 and 282 us); 260 of
+//    100 rows, G = 2: 19.4 and 16.5 us.
+//  * Long units whose work-groups would leave the chip a quarter empty or more (257 to 383 units of
+//    four waves, 513 to 767 of two) and those whose LDS would not fit: one-wave splits with records.
+//    260 units of 7040 rows, G = 12, without offset: 1015 us shared, 778 us by splits; 372 ragged units
+//    of up to 4100 rows, G = 6: 143 and 121 us.
 AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
   const int64_t cap = (int64_t)ns * sr, U = p->num_units;  // every plan covers the same rows
   const int gb = std::min(p->group, kHeadBlock);
@@ -167,9 +176,20 @@ AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
   if (cap <= kWaveMinRows) return {1, 1, sr, 0};
   const int32_t wpg = U <= 256 ? 8 : U <= 512 ? 4 : 2;
   const size_t lds_max = kUnitLdsMax * (size_t)wpg / kUnitWaves;  // so that 8 waves share a CU
+  if (cap <= (U > 1024 ? kWholeRowsMany : kSplitRowsLimit) &&
+      attend_fused_lds_bytes((int32_t)cap, gb) <= kSplitLdsBudget) {
+    // us: 16 rows take a wave 0.75 us, 1.35 us with another one on its SIMD; a shared unit's waves
+    // combine their sums and finalize their heads one after the other, 11 us each, a lone wave all
+    // its heads together
+    const double tiles = (double)cap / 16.0;
+    const double shared = tiles / wpg * 1.35 * std::ceil((double)U * wpg / kResidentWaves) + 6.0 +
+                          11.0 * ((gb + wpg - 1) / wpg);
+    const double whole = tiles * (U > 1024 ? 1.35 : 0.75) + 10.5 + 0.5 * gb;
+    if (whole < shared) return {1, 1, (int32_t)((cap + 15) / 16 * 16), 0};
+  }
+  if (U > 256 && U * wpg < kSplitWaves && cap > kLongRows) return {ns, 1, sr, 0};
   int64_t parts = 1;
-  if (U < 256 && cap > kUnitRowsMax)
-    parts = std::max<int64_t>(1, std::min<int64_t>(256 / U, cap / (kPartWaveRows * wpg)));
+  if (U < 256) parts = std::max<int64_t>(1, std::min<int64_t>(256 / U, cap / (kPartWaveRows * wpg)));
   const int64_t room = (int64_t)ns * attend_record_floats(sr);  // per (unit, head)
   // fewest parts that the LDS allows, at least the wanted ones, then fewer while records exceed
   // the workspace
@@ -179,6 +199,7 @@ AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
     ++parts;
   while (parts > 1 && parts * part_record_floats(rows_of(parts), wpg) > room) --parts;
   const int32_t rows = rows_of(parts);
+  if (parts > 1 && U > 256) return {ns, 1, sr, 0};  // more waves than the chip holds: one-wave splits
   if (rows > kSplitRowsLimit || attend_shared_lds_bytes(rows, wpg, gb, parts > 1) > lds_max || parts >= kMaxSplits)
     return {ns, 1, sr, 0};  // records of one-wave splits
   return {(int32_t)parts, wpg, std::max(rows, kWaveMinRows), 1};

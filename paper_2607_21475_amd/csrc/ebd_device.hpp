@@ -85,6 +85,18 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
+// x plus its value in lane ^ 8, ^ 16, ^ 32 (row_ror:8, then the row swaps of gfx950), without the LDS
+// crossbar that __shfl_xor goes through.
+__device__ __forceinline__ float add_xor8(float x) { return x + dpp_f<0x128>(x); }
+__device__ __forceinline__ float add_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Wave reductions: DPP within each 16-lane row (every lane of a row gets the row's result), then
 // the four row results by lane reads, so the result is the same in every lane and the order of
 // the operations is fixed.  Every lane of the wave must be active.
@@ -143,6 +155,9 @@ __device__ __forceinline__ double wave_sum(double x) {
 }
 __device__ __forceinline__ int wave_sum(int x) {
   return wave_reduce(x, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_min(int x) {
+  return wave_reduce(x, [](int a, int b) { return a < b ? a : b; });
 }
 __device__ __forceinline__ float wave_max(float x) {
   return wave_reduce(x, [](float a, float b) { return fmaxf(a, b); });
