@@ -157,9 +157,9 @@ int64_t part_record_floats(int32_t rows, int32_t wpg) {
 //    rows, G = 7: 57.6 and 40.1 us; 128 units of 2140 rows: 49.6 and 46.6 us; one part (1025 rows): 32.4 us.
 //    Short units are quicker by a wave each (the estimate below), above all where a work-group has
 //    fewer waves than heads: 755 units of up to 400 rows, G = 8: 66 us shared, 35 us by a wave each;
-//    527 of up to 340 rows, G = 3: 42 and 31 us; 1286 of up to 960 rows, G = 6: 132 and 90 us (from 2560 rows on two
-//    waves win there: 1124 ragged units of up to 3600 rows 275 and 282 us); 260 of
-//    100 rows, G = 2: 19.4 and 16.5 us.
+//    527 of up to 340 rows, G = 3: 42 and 31 us; 260 of 100 rows, G = 2: 19.4 and 16.5 us; 1286 of up to
+//    960 rows, G = 6: 132 and 90 us; 1100 of 1800 rows, G = 8: 258 and 201 us (from 2560 rows on two
+//    waves win there: 1124 ragged units of up to 3600 rows 275 and 282 us).
 //  * Long units whose work-groups would leave the chip a quarter empty or more (257 to 383 units of
 //    four waves, 513 to 767 of two) and those whose LDS would not fit: one-wave splits with records.
 //    260 units of 7040 rows, G = 12, without offset: 1015 us shared, 778 us by splits; 372 ragged units

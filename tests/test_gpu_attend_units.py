@@ -45,9 +45,9 @@ def _units(sizes, G, seed, dominant=0):
 @pytest.mark.parametrize("sizes,G,dominant", [
     ([1], 1, 0),                                   # one row
     ([15, 16, 17, 0, 31, 32, 33, 255, 256, 257], 4, 0),   # tiles and waves with nothing to do
-    ([2000, 3584, 129, 0, 3583], 1, 0),            # the longest single-part units
+    ([2000, 3584, 129, 0, 3583], 1, 0),            # parts, the last of them short or empty
     ([3584, 700, 127], 8, 2),
-    ([3585, 40, 0, 1500, 3000], 4, 0),             # just past them: parts, some of them empty
+    ([3585, 40, 0, 1500, 3000], 4, 0),             # one tile more
     ([13100] * 4, 4, 6),                           # parts with pivots added back in each
     ([13100, 6000, 97], 7, 6),
     ([9000] * 3, 8, 0),
