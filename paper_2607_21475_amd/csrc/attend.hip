@@ -1340,7 +1340,7 @@ __global__ __launch_bounds__(SHARED ? 64 * kUnitWaves : 64, 2) void attend_split
   if (L.status && sp == 0 && h0 == 0 && lane == 0 && !L.plain)
     L.status[u] = ((int64_t)L.count[u] > cap ? EBD_ST_CAP_OVERFLOW : 0u) |
                   (held > (int64_t)cnt ? EBD_ST_BAD_LAYOUT : 0u);
-  if (cnt == 0) {  // an empty unit gets empty outputs
+  if (cnt <= 0) {  // an empty unit gets empty outputs (also one whose count is negative)
     if (sp == 0) finalize_empty<GB>(L, u, h0);
     return;
   }
@@ -1556,7 +1556,7 @@ void attend_finalize_kernel(AttendLaunch L) {
   const int64_t cbase = L.cap_off[u];
   const int64_t cap = L.cap_off[u + 1] - cbase;
   const int cnt = (int)min(min((int64_t)L.count[u], cap), (int64_t)L.seen);
-  if (cnt == 0) return;  // its outputs are written already
+  if (cnt <= 0) return;  // its outputs are written already
   const int r = wave_rows(L, cnt);
   const int nsp = (cnt + r * L.wpg - 1) / (r * L.wpg);
   const float *rec0 = L.part + ((int64_t)u * L.nsplit * L.G + h) * L.rec;

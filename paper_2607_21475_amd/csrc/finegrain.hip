@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_contrib_kernel(BlocksL
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int64_t cbase = L.cap_off[u];
   const int64_t cap = L.cap_off[u + 1] - cbase;
-  const int cnt = (int)min(min((int64_t)L.count[u], cap), L.max_rows);
+  const int cnt = max((int)min(min((int64_t)L.count[u], cap), L.max_rows), 0);
   const int64_t uh0 = (int64_t)u * L.G + h0;
 
   for (int64_t b = lane; b < L.nblocks; b += 64) s_bin[b] = 0.0f;

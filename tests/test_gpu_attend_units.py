@@ -113,3 +113,31 @@ def test_attend_library_plans_without_offset(sizes, G):
         y = torch.softmax(lg, 1) @ rc.Vc[off[u]:off[u] + n].double()
         assert torch.linalg.norm(res["y"][u].double() - y) <= 1e-4 * torch.linalg.norm(y)
         assert torch.all((res["lse"][u].double() - torch.logsumexp(lg, 1)).abs() <= 1e-4)
+
+
+@pytest.mark.parametrize("units,n,split", [(4, 200, 0), (4, 9000, 0), (1540, 100, 0), (6, 400, 16), (6, 400, 64)])
+def test_negative_counts_are_empty_units(units, n, split):
+    """A unit whose count is negative holds no rows in every launch mode (waves sharing a unit, parts,
+    a wave per unit, one-wave records, the caller's splits in one work-group): empty outputs, and no
+    block contributions."""
+    import paper_2607_21475_amd as ebd
+    from paper_2607_21475_amd import cache
+
+    _say("attend negative counts units=%d n=%d split=%d" % (units, n, split))
+    rc, q = _units([n] * units, 4, seed=units)
+    want = cache.attend_certify(rc, q, split_rows=split)
+    rc.count[1::2] = torch.tensor([-1, -(2 ** 31)], dtype=torch.int32, device="cuda").repeat(units)[:units // 2]
+    p = ebd.attend_params(units, 4, rc.max_cap, rc.cap_off, split)
+    res = {k: torch.full_like(v, 7) for k, v in want.items() if k != "ws"}
+    ebd.ebd_attend_certify(p, q, rc.Kc, rc.Vc, rc.pic, rc.count, res["y"], res["vhat"], res["lse"], want["ws"],
+                           brange=res["b"], radius=res["r"], status=res["status"])
+    blocks = torch.full((units, 8), 7.0, device="cuda")
+    ebd.ebd_block_contributions(units, 4, 8, rc.max_cap, rc.cap_off, q, rc.Kc, rc.Vc, rc.pic, rc.idxc, rc.count,
+                                res["y"], res["lse"], blocks)
+    torch.cuda.synchronize()
+    for k in ("y", "vhat", "lse", "b", "r"):
+        assert torch.equal(res[k][0::2], want[k][0::2]), k
+    for k in ("y", "vhat", "b", "r", "status"):
+        assert not res[k][1::2].any(), k
+    assert torch.all(torch.isneginf(res["lse"][1::2]))
+    assert not blocks[1::2].any() and torch.all(blocks[0::2, 0] > 0)
