@@ -161,22 +161,25 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
   const int64_t tail_lo = L.n_sink, tail_hi = U.n - (int64_t)L.n_recent;
   const double n_tail = (double)max(tail_hi - tail_lo, (int64_t)0);
   int rb = 0;
-  auto bsum = [&](double a, double b, double c, double &A, double &B, double &C) {
-    a = wave_sum(a);
-    b = wave_sum(b);
+  // The work-group's totals of two counts (below 2^24: they share one exact double) and two sums.
+  auto bsum = [&](int a, int b, double c, double d, double &A, double &B, double &C, double &D) {
+    double x = wave_sum((double)a + (double)b * 16777216.0);
     c = wave_sum(c);
+    d = wave_sum(d);
     if (lane == 0) {
-      s_red[rb][wv][0] = a;
-      s_red[rb][wv][1] = b;
-      s_red[rb][wv][2] = c;
+      s_red[rb][wv][0] = x;
+      s_red[rb][wv][1] = c;
+      s_red[rb][wv][2] = d;
     }
     __syncthreads();
-    A = B = C = 0.0;
+    x = C = D = 0.0;
     for (int w = 0; w < NW; ++w) {
-      A += s_red[rb][w][0];
-      B += s_red[rb][w][1];
-      C += s_red[rb][w][2];
+      x += s_red[rb][w][0];
+      C += s_red[rb][w][1];
+      D += s_red[rb][w][2];
     }
+    B = floor(x * (1.0 / 16777216.0));
+    A = x - B * 16777216.0;
     rb ^= 1;
   };
 
@@ -286,12 +289,17 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
     const double start = best >= 0 ? s_red[0][0][0] : m / s_sum;
     __syncthreads();
 
-    // What the list of scores around the thresholds covers, and g's terms of everything else.
+    // What the list of scores around the thresholds covers, and g's terms of everything else.  The
+    // list's order follows its atomics.  The middle scores of the upper threshold's bins (from `split`
+    // on) and those of the lower one's are summed apart: five bins share two exponents, so up to
+    // kSolveList of their scores are summed exactly in double (40 bits), in any order, however far
+    // apart eps puts the two.
     const float *sc = L.scores + U.base;
     const bool vec = (U.base & 3) == 0;
     int c1 = -1, c0 = -1;  // bins of the thresholds it was collected around
     bool listed = false;
     double bH = 0.0, bL = 0.0, bS = 0.0;
+    float split = 0.0f;
     auto for_tail = [&](auto &&fn) {  // every cleaned tail score
       const int64_t nq = (U.n + 3) / 4;
       for (int64_t g0 = 0; g0 < nq; g0 += 4 * NT) {
@@ -314,6 +322,7 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
     auto collect = [&](int b1, int b0) {
       c1 = b1;
       c0 = b0;
+      split = bin_low(max(b1 - kBinReach, 0));
       const int r1 = b1 - kBinReach, R1 = b1 + kBinReach, r0 = b0 - kBinReach, R0 = b0 + kBinReach;
       if (t == 0) s_n = 0;
       __syncthreads();
@@ -324,15 +333,16 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
           if (k < kSolveList) s_list[k] = c;
         }
       });
-      double H = 0.0, Lo = 0.0, S = 0.0;
+      int H = 0, Lo = 0;
+      double S = 0.0, none;
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int b = PER * t + k;
-        if (b > R1) H += (double)(hv[k] >> kLowBits);
-        else if (b < r0) Lo += (double)(hv[k] >> kLowBits);
+        if (b > R1) H += (int)(hv[k] >> kLowBits);
+        else if (b < r0) Lo += (int)(hv[k] >> kLowBits);
         else if (b > R0 && b < r1) S += bin_sum(b, hv[k]);
       }
-      bsum(H, Lo, S, bH, bL, bS);  // its barrier also completes the list
+      bsum(H, Lo, S, 0.0, bH, bL, bS, none);  // its barrier also completes the list
       bL += n_zero;
       listed = s_n <= kSolveList;
     };
@@ -346,13 +356,16 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
         __syncthreads();  // every thread is done with the list
         collect(b1, b0);
       }
-      double H = 0.0, Lo = 0.0, S = 0.0;
+      int H = 0, Lo = 0;
+      double S1 = 0.0, S0 = 0.0;  // the middle at and above `split`, and below it
       auto add = [&](float s) {
         const float p = lf * s;
         const bool hb = p >= 1.0f, lb = p <= eps;
-        H += hb ? 1.0 : 0.0;
-        Lo += lb ? 1.0 : 0.0;
-        S += (hb || lb) ? 0.0 : (double)s;
+        H += hb ? 1 : 0;
+        Lo += lb ? 1 : 0;
+        const double mid = (hb || lb) ? 0.0 : (double)s;
+        if (s >= split) S1 += mid;
+        else S0 += mid;
       };
       const bool from_list = !far && listed;
       if (from_list) {
@@ -360,7 +373,8 @@ __global__ __launch_bounds__(kSolveThreads) void evict_long_solve_kernel(EvictLa
       } else {
         for_tail(add);  // more scores around the thresholds than the list holds
       }
-      bsum(H, Lo, S, dH, dL, dS);
+      bsum(H, Lo, S1, S0, dH, dL, S1, S0);
+      dS = S1 + S0;
       if (from_list) {
         dH += bH;
         dL += bL;

@@ -25,6 +25,8 @@ def _scores(kind, rows, seed):
         s = torch.rand(rows, generator=g, device="cuda")
         e = torch.randint(-145, 120, (rows,), generator=g, device="cuda").float()
         return torch.where(s < 0.9, torch.zeros_like(s), torch.ldexp(s, e))
+    if kind == "wide":  # spread evenly over 40 octaves: scores around both thresholds however far apart
+        return torch.exp2(-40.0 * torch.rand(rows, generator=g, device="cuda"))
     s = torch.rand(rows, generator=g, device="cuda")  # "bad": a few values read as zero
     s[7], s[rows // 2], s[rows - 3] = float("nan"), -1.0, float("inf")
     return s
@@ -43,6 +45,7 @@ def _scores(kind, rows, seed):
     ([20000] * 2, "lognormal", 0.25, 0.01, 1),                # lambda = m / sum s
     ([20000], "lognormal", 0.6, 0.9, 0),                      # thresholds in neighbouring bins
     ([17000] * 40, "pareto", 0.5, 0.01, 0),
+    ([60000, 131072], "wide", 0.05, 1e-6, 0),                 # thresholds 20 octaves apart
 ])
 def test_evict_long_parity(lengths, kind, budget, eps, mode):
     _say("evict long lengths=%s %s budget=%s" % (lengths[:4], kind, budget))
@@ -58,6 +61,15 @@ def test_evict_long_parity(lengths, kind, budget, eps, mode):
                          None, eps, mode, 9)
     assert ebd.ebd_workspace_size(ebd.EBD_WS_EVICT, p) > 256
     _check_evict(lengths, K, V, seq_off, sc, out, budget=budget, pi_min=eps, seed=9, pi_mode=mode)
+    # again: the same bits, whatever order the scores around the thresholds were collected in
+    again = _evict(K, V, seq_off, sc, lengths, cap_off_host=cap, **kw)
+    off = _np(out.cap_off)
+    for k in ("count", "status", "lam", "pi_full"):
+        assert torch.equal(getattr(out, k), getattr(again, k)), k
+    for u in range(len(lengths)):
+        sl = slice(off[u], off[u] + int(out.count[u]))
+        for k in ("Kc", "Vc", "pic", "idxc"):
+            assert torch.equal(getattr(out, k)[sl], getattr(again, k)[sl]), (u, k)
     # the same call with a 256-byte workspace: a work-group per unit
     ref = {k: torch.zeros_like(getattr(out, k)) for k in ("Kc", "Vc", "pic", "idxc", "count", "status", "lam")}
     pf = torch.zeros_like(out.pi_full)
@@ -70,7 +82,6 @@ def test_evict_long_parity(lengths, kind, budget, eps, mode):
     with np.errstate(invalid="ignore"):  # +inf where nothing is evicted
         same = (lam == rlam) | (np.abs(lam - rlam) <= 3e-7 * np.abs(rlam))
     assert np.all(same), (lam, rlam)
-    off = _np(out.cap_off)
     for u in np.nonzero(lam == rlam)[0]:
         n = int(ref["count"][u])
         assert n == int(out.count[u])
