@@ -353,6 +353,21 @@ def _outputs(torch, U, G):
                          ("r", (U, G)))}
 
 
+def _shares_gather(copies: int, n: int) -> bool:
+    """Whether an eviction that launched evict_copy gathered part of its rows in evict_select: units
+    longer than the register kernels hold (6144 tokens) may; how many rows each took is not reported."""
+    return copies > 0 and n > 6144
+
+
+def _join_evict(kt, alg):
+    """Where evict_select and evict_copy share the gather only their bytes together are known: one
+    more row for the two."""
+    both = "evict_select+evict_copy"
+    kt[both] = (kt["evict_select"][0] + kt["evict_copy"][0], kt["evict_select"][1])
+    alg[both] = alg["evict_select"] + alg["evict_copy"]
+    alg["evict_select"] = alg["evict_copy"] = None
+
+
 def _kernel_table(kt, alg, steps):
     """Per kernel: total and average launch time (HIP events on the launch stream) and the
     achieved rate of its algorithmic bytes."""
@@ -361,15 +376,17 @@ def _kernel_table(kt, alg, steps):
         if launches == 0:
             continue
         avg_ms = ms / launches
+        kern[k] = dict(total_ms=round(ms, 4), launches=int(launches), avg_us=round(avg_ms * 1e3, 2))
+        if alg[k] is None:
+            continue
         gbs = alg[k] * steps / (ms * 1e-3) / 1e9
-        kern[k] = dict(total_ms=round(ms, 4), launches=int(launches), avg_us=round(avg_ms * 1e3, 2),
-                       alg_bytes_per_step=int(alg[k]), achieved_gbs=round(gbs, 1),
+        kern[k].update(alg_bytes_per_step=int(alg[k]), achieved_gbs=round(gbs, 1),
                        frac_hbm=round(gbs / HBM_PEAK_GBS, 4))
     return kern
 
 
 def _roofline(kern, alg, steps, workload):
-    dom = max(kern, key=lambda k: kern[k]["total_ms"])
+    dom = max((k for k in kern if alg[k] is not None and "+" not in k), key=lambda k: kern[k]["total_ms"])
     dk = kern[dom]
     launch_bytes = alg[dom] / (dk["launches"] / steps)
     return {"bound": "hbm", "achieved": dk["achieved_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -468,8 +485,11 @@ def decode_leg(wl, args, headline: bool):
         "attend_split": 516 * att_rows + T * U * G * 256 + (T * U * G * 528 if fused else 0),
         "attend_finalize": 0 if fused else T * U * G * 528,
     }
-    kern = _kernel_table(kt, alg, K)
     t_evict_k = (kt["evict_select"][0] + kt["evict_copy"][0]) * 1e-3
+    shares = _shares_gather(kt["evict_copy"][1], n)
+    if shares:
+        _join_evict(kt, alg)
+    kern = _kernel_table(kt, alg, K)
     leg = {
         "value": round(value, 1),
         "unit": "GB/s",
@@ -490,7 +510,7 @@ def decode_leg(wl, args, headline: bool):
         "retained_rows_after_eviction": rows0,
         "mean_retained_per_unit": round(rows0 / U, 1),
         "fused_finalize": bool(fused),
-        "evict_select_gathers": bool(gathers),
+        "evict_select_gathers": "in part" if shares else bool(gathers),
         "range_term_rescans_last_step": cache.rescans(aws, U, G),
         "direct_variance_heads_last_step": cache.direct_variances(aws, U, G),
         "kernels": kern,
@@ -560,7 +580,7 @@ def budgets_leg(wl, args, headline: bool):
         attend_all()
     torch.cuda.synchronize()
     ebd.ebd_timing_enable(True)
-    for p in plans:  # which budgets' evictions gather their rows inside evict_select
+    for p in plans:  # which budgets' evictions gather (all) their rows inside evict_select
         ebd.ebd_timing_read("evict_copy")
         rc = p["rc"]
         ebd.ebd_evict(p["ep"], inp["scores"], inp["K"], inp["V"], rc.Kc, rc.Vc, rc.pic, rc.idxc,
@@ -614,6 +634,8 @@ def budgets_leg(wl, args, headline: bool):
         "attend_split": 516 * retained_total + nb * U * G * 256 + nfused * U * G * 528,
         "attend_finalize": (nb - nfused) * U * G * 528,
     }
+    if any(_shares_gather(0 if p["gathers"] else 1, n) for p in plans):
+        _join_evict(kt, alg)
     kern = _kernel_table(kt, alg, K)
     value = 512 * retained_total * K / (attend_ms * 1e-3) / 1e9
     leg = {

@@ -128,9 +128,9 @@ typedef struct ebd_evict_params {
  *   workspace: at least ebd_workspace_size(EBD_WS_EVICT, p) bytes, 256-byte aligned
  *   (256 bytes, reserved, except for Poisson launches of fewer than 768 units longer than 16384
  *   tokens: about 64 KB per unit, for which 256 bytes are still accepted, at a lower speed).
- *   A call takes one kernel where the selection also gathers the rows, two where the gather is a
- *   launch of its own ("evict_copy") or a large unit's later rows are (timed with "evict_select"), five
- *   for the long units above.
+ *   A call takes one kernel ("evict_select") where the selection also gathers the rows, two where the
+ *   gather, or that of a large unit's later rows, is a launch of its own ("evict_copy"), five for the
+ *   long units above (timed as "evict_select", and the last, which gathers, as "evict_copy").
  *   Rows of Kc/Vc/pic/idxc beyond count[u] are left untouched.
  */
 ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint16_t *K,

@@ -435,14 +435,8 @@ ebd_status ebd_evict(const ebd_evict_params *p, const float *scores, const uint1
       return EBD_ERR_HIP;
     return EBD_OK;
   }
-  // the rows that a gathering selection leaves to evict_copy count as its own launch's
-  const bool rest = L.gather > 0 && L.copy_blocks > L.gather / kCopyRows;
-  if (timed("evict_select", s, [&] {
-        const hipError_t e = launch_evict_select(L, s);
-        return e == hipSuccess && rest ? launch_evict_copy(L, s) : e;
-      }) != hipSuccess)
-    return EBD_ERR_HIP;
-  if (L.copy_blocks > 0 && L.gather == 0 &&
+  if (timed("evict_select", s, [&] { return launch_evict_select(L, s); }) != hipSuccess) return EBD_ERR_HIP;
+  if (L.copy_blocks > L.gather / kCopyRows &&
       timed("evict_copy", s, [&] { return launch_evict_copy(L, s); }) != hipSuccess)
     return EBD_ERR_HIP;
   return EBD_OK;

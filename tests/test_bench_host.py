@@ -69,3 +69,19 @@ def test_committed_traffic_is_used_only_while_the_sources_match():
     else:
         assert got is None
     assert bench.load_traffic("no_such_workload", "evict_copy") is None
+
+
+def test_a_gather_shared_by_two_kernels_is_rated_as_one():
+    """Units longer than the register kernels hold may be gathered partly by evict_select: the bytes of
+    the two launches are only known together, and neither is credited with them alone."""
+    assert bench._shares_gather(3, 16384) and not bench._shares_gather(3, 6144)
+    assert not bench._shares_gather(0, 16384)
+    kt = {"evict_select": (6.0, 3), "evict_copy": (3.0, 3), "attend_split": (8.0, 3)}
+    alg = {"evict_select": 10 ** 9, "evict_copy": 2 * 10 ** 9, "attend_split": 4 * 10 ** 9}
+    bench._join_evict(kt, alg)
+    kern = bench._kernel_table(kt, alg, 3)
+    assert "achieved_gbs" not in kern["evict_select"] and "achieved_gbs" not in kern["evict_copy"]
+    both = kern["evict_select+evict_copy"]
+    assert both["launches"] == 3 and both["alg_bytes_per_step"] == 3 * 10 ** 9
+    assert both["achieved_gbs"] == 1000.0  # 9e9 bytes in 9 ms
+    assert bench._roofline(kern, alg, 3, "unit_test")["kernel"] == "attend_split"
