@@ -2,10 +2,11 @@
 // Sec. 3.1: evicted rows are deleted, retained rows keep one stored pi each).
 //
 // Launches per call:
-//   evict_select_reg (units of at most 6144 tokens of large launches, of at most 2048 of small ones)
-//                 one work-group of 2 waves per unit, the scores in registers, so that
-//                 every unit of a large batch is resident at once; the same steps as evict_select
-//                 below with one barrier per reduction or prefix; then evict_copy gathers the rows.
+//   evict_select_reg (units of at most 6144 tokens of large launches, of at most 2048 of small ones:
+//                 evict_select_in_regs) one work-group of 2 waves per unit, the scores in
+//                 registers, so that every unit of a large batch is resident at once; the same steps as
+//                 evict_select below with one barrier per reduction or prefix; then evict_copy gathers
+//                 the rows.
 //   evict_select  (other launches) one work-group of 8 waves per unit, two per CU.  Stages the
 //                 unit's scores in LDS (up to 16384 tokens, protected positions marked by a
 //                 negative sentinel; longer units are re-read from memory), solves lambda with
@@ -16,9 +17,9 @@
 //                 (fixed-size systematic design), or the score threshold of a radix select (top-k
 //                 comparison design); ballot ranks plus a cross-wave prefix give the order in
 //                 which the stored pi and original position of every retained row are written,
-//                 plus the count and status bits.  In large launches the same work-group then
-//                 gathers its unit's first retained K and V rows (the gathers of some units overlap
-//                 the selection of others), and evict_copy those past evict_gather_rows.
+//                 plus the count and status bits.  The same work-group then gathers the unit's
+//                 first evict_gather_rows retained K and V rows (in large launches the gathers of
+//                 some units overlap the selection of others), and evict_copy those past them.
 //   evict_long_*  (evict_long.hip: few units longer than LDS holds) every pass by segments.
 //   evict_copy    one work-group per (unit, block of retained rows): gathers the retained K and
 //                 V rows named by the index list (16 lanes x 16 B per 256-byte row, all loads of
@@ -1189,43 +1190,50 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
   }
 }
 
-// Whether evict_select's own work-groups gather their units' rows, or a copy launch follows.  With
-// many units the gathers of some overlap the latency-bound selection of others, which wins while
-// there are few rows to gather (a capacity under a sixth of the length) or the selection is long
-// (units past the register kernel): 1024 units of 16384 tokens, 10% / 25%: 348 / 862 us against
-// 403 / 882 us.  With fewer units than CUs most of the chip would watch the gather: 64 units of 16384
-// tokens, 25%: 137 against 90 us; 8 units of 8192 tokens: 56 against 29 us (up to 512 rows the launch
-// costs more than it saves: 181 units of up to 325 rows 26.7 against 23.1 us); in between the copy
-// launch wins from 25% on (256 units of 16384 tokens, 10 / 25 / 50%: 110 / 225 / 431 against 117 /
-// 221 / 400 us).
-//
-// A gathering work-group takes evict_gather_rows of its unit's rows and evict_copy, which fills the
-// chip whatever the units' sizes, the others: where lengths and budgets differ, a unit selected late
-// with eight times the mean's rows was gathered by one CU while the others had finished.  A sixteenth
-// of the longest unit, 1024 to 4096 rows, is enough to cover the others' selection: 1008 units of 2048
-// to 16384 tokens at 5 to 50%: all rows 500, first 4096 / 2048 / 1024 / 512 rows 431 / 388 / 370 /
-// 375 us; 800 units of up to 131072 tokens: all 3618, first 16384 / 8192 / 4096 / 1024 rows 2906 / 2724 /
-// 2713 / 2851 us; equal units of 16384 tokens, 25%: 740 against 743 us.  Up to twice that many rows a
-// unit is gathered whole (2048 units of 16384 tokens, 10%: 651 us, 668 with a launch for the rest).
+// Rows of each unit that its own evict_select work-group gathers; evict_copy, which fills the chip
+// whatever the units' sizes, takes the others.  Times in us of whole calls, back to back on the same
+// buffers; "few" rows: a capacity under a sixth of the longest unit.
+//  * Fewer than 256 units: the copy launch, but for few rows that cost less than the launch (up to 512 of
+//    each unit, and the more the fuller the chip is of units: U^2 / 15): 8 units of 1024 tokens, 5%:
+//    gathered 10, copied 13; 181 of 4096, 10%: 31 and 35; 255 ragged of up to 16384, 10%: 83 and 99; but
+//    64 of 4096, 10%: 27 and 25; 64 of 16384, 10%: 75 and 59; 128 ragged of up to 8192, 10%: 43 and 41.
+//    (Two waves per unit and a copy, at 2048 tokens: 64 units, 5%: gathered 18, copied 17.)
+//  * Few rows of 256 units and more are gathered whole (the gathers of some overlap the latency-bound
+//    selection of others), up to three shares (below): 767 units of 16384 tokens, 10%: 290, copied 323, shared
+//    303; 512 of 20000: 273, 283 and 279.  Streamed units of more than 128 tokens for every unit of
+//    the launch gain more from the copy: 300 of 65536, 10%, top-k: 721 and 617; but 512 of 33000: 439 and 445.
+//  * More rows: the copy launch wherever the register kernel selects, up to 512 units that are staged in
+//    LDS and 320 that are streamed (25%: 400 units of 16384 tokens, copied 361, shared 371, and ragged 226
+//    and 218; 600: 542 and 542; 300 of 16385: 317 and 326; 512: 484 and 480, and ragged 273 and 265); else a
+//    sixteenth of the longest unit, 1024 to 4096 rows, is gathered, enough to cover the others'
+//    selection (1008 units of up to 16384 tokens at 5 to 50%: gathered whole 573, copied 471, shared 428).
+//    Up to twice that many rows a unit is gathered whole.
 int32_t evict_gather_rows(const EvictLaunch &L) {
-  const int64_t capacity = (int64_t)L.copy_blocks * kCopyRows;
-  const bool few_rows = capacity * 6 < L.max_rows;
-  if (L.U < 256) return few_rows && capacity <= kGatherFewRows && L.max_rows > kRegRowsMax / 3 ? (int32_t)capacity : 0;
-  if (L.U < kEvictManyUnits) {
-    if (!few_rows || L.max_rows > kEvictStageMax) return 0;
-  } else if (!few_rows && L.max_rows <= kRegRowsMax) {
-    return 0;
+  const int64_t capacity = (int64_t)L.copy_blocks * kCopyRows, U = L.U, n = L.max_rows;
+  const bool few = evict_few_rows(capacity, n);
+  if (U < 256) {
+    const bool mid = n > kRegRowsMax / 6 && n <= kRegRowsMax / 3;
+    const int64_t most = U * U / 15 < kGatherFewRows ? kGatherFewRows : U * U / 15;
+    return few && !mid && capacity <= most ? (int32_t)capacity : 0;
   }
-  const int64_t share = L.max_rows / 16 / kCopyRows * kCopyRows;
+  const bool streamed = n > kEvictStageMax;
+  if (few ? streamed && n > 128 * U : n <= kRegRowsMax || U <= (streamed ? 320 : 512)) return 0;
+  const int64_t share = n / 16 / kCopyRows * kCopyRows;
   const int64_t first = share < kGatherMinRows ? kGatherMinRows : share > kGatherMaxRows ? kGatherMaxRows : share;
-  return (int32_t)(capacity <= 2 * first ? 2 * first : first);
+  return (int32_t)(capacity <= (few ? 3 : 2) * first ? capacity : first);
 }
 
 // The two-wave register kernel keeps every unit of a large launch resident at once; a small launch has
-// room for eight waves per unit, which are faster from 4096 tokens on (8 units of 6144 tokens: 23
-// against 28 us; at 2048 tokens 16 against 14 us).
+// room for eight waves per unit, which are faster from 2049 tokens on up to 256 units (256 units of 4096
+// tokens, 25%: 69 against 71 us; 8 of 6144: 26 against 32; of 2048: 19 against 16), from 4097 on up
+// to 512 (400 units, 25%: 4096 tokens 102.5 against 101.5 us, 6144 tokens 146 against 149; 600 of 6144: 219
+// against 210), there from 2049 on for the systematic design, whose weights take another pass (512
+// units of 3000 tokens, 10%: 59 against 63 us; 600: 76 against 72).
 bool evict_select_in_regs(const EvictLaunch &L) {
-  return !L.gather && L.max_rows <= (L.U >= kEvictManyUnits ? kRegRowsMax : kRegRowsMax / 3);
+  const int64_t most = L.U > 512                                              ? kRegRowsMax
+                       : L.U > 256 && L.design != EBD_DESIGN_SYSTEMATIC ? kRegRowsMax * 2 / 3
+                                                                        : kRegRowsMax / 3;
+  return !L.gather && L.max_rows <= most;
 }
 
 hipError_t launch_evict_select(const EvictLaunch &L, hipStream_t s) {

@@ -23,8 +23,19 @@ def _launches(names, call):
 
 
 @pytest.mark.parametrize("units,n,budget,design,copies", [
-    (800, 8192, 0.25, 0, 1),     # the selection gathers a share, the copy the rest
-    (800, 8192, 0.10, 0, 0),     # few rows: gathered whole
+    (8, 1024, 0.05, 0, 0),      # a few rows: gathered by the selection
+    (8, 2048, 0.05, 0, 1),      # two waves per unit, then the copy
+    (64, 4096, 0.10, 0, 1),     # 640 rows: worth a copy launch for 64 units
+    (181, 4096, 0.10, 0, 0),    # ... not for 181
+    (255, 16384, 0.10, 0, 0),
+    (300, 4096, 0.25, 0, 1),
+    (300, 4096, 0.10, 0, 0),    # few rows: gathered whole
+    (300, 16384, 0.25, 0, 1),
+    (600, 8192, 0.10, 0, 0),
+    (600, 8192, 0.25, 0, 1),    # the selection gathers a share, the copy the rest
+    (330, 16400, 0.10, 0, 0),   # streamed units past those of the segment kernels
+    (330, 16400, 0.10, 1, 0),
+    (300, 16400, 0.25, 2, 1),
 ])
 def test_evict_gather_launches(units, n, budget, design, copies):
     _say("evict launches units=%d n=%d budget=%s design=%d" % (units, n, budget, design))
