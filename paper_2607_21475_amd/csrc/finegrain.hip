@@ -3,9 +3,10 @@
 // averaged over sampled heads and maximized over decode steps).
 //
 // block_contrib  one work-group per (unit, block of <= 8 query heads), up to 8 waves that take the
-//                unit's tiles of 16 retained rows in turn, on MFMA: kappa_hj = (1 - pi_j) (a_hj / (pi_j Nhat_h))^2 |v_j - yhat_h|^2, the
-//                summand of Theorem 2, with a/(pi Nhat) = exp(scale q.k - ln pi - ln Nhat) from
-//                the certified attention's own outputs; summed over the heads and into the wave's
+//                unit's tiles of 16 retained rows in turn, on MFMA:
+//                kappa_hj = (1 - pi_j) (a_hj / (pi_j Nhat_h))^2 |v_j - yhat_h|^2, the summand of
+//                Theorem 2, with a/(pi Nhat) = exp(scale q.k - ln pi - ln Nhat) from the
+//                certified attention's own outputs; summed over the heads and into the wave's
 //                LDS bin of the row's original position / block_rows; the waves' bins are summed
 //                in order and written (first head block) or added (later head blocks, launched in
 //                order) to the unit's blocks.
@@ -56,10 +57,12 @@ __device__ __forceinline__ uint32_t bf16_top(float x) { return __float_as_uint(x
 // yhat), the tile recomputes the squared distance directly.  Lane (g, c) holds heads 4g .. 4g+3
 // for row 16t + c; the heads' terms are summed over the four row groups and added to the LDS bin
 // of the row's original position.
-template <int GB>
-__global__ __launch_bounds__(64 * kBlockWaves) void block_contrib_kernel(BlocksLaunch L, int h0) {
+template <int GB, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 64 * kBlockWaves : 64, 2) void block_contrib_kernel(BlocksLaunch L,
+                                                                                         int h0) {
   extern __shared__ float s_all[];  // [waves][nblocks], then |yhat|^2 [8], ln Nhat [8], yhat [GB][128]
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nw = (int)(blockDim.x >> 6);
+  const int wave = SHARED ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int nw = SHARED ? (int)(blockDim.x >> 6) : 1;
   float *s_bin = s_all + (int64_t)wave * L.nblocks;  // this wave's bins
   float *s_yy = s_all + (int64_t)nw * L.nblocks;
   float *s_l = s_yy + 8;
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_contrib_kernel(BlocksL
     s_yy[c] = c < GB ? yy : 0.0f;
     s_l[c] = c < GB ? L.lse[uh0 + c] : 0.0f;
   }
-  for (int e = threadIdx.x; e < GB * kHeadDim; e += blockDim.x) s_y[e] = L.y[uh0 * kHeadDim + e];
+  for (int e = threadIdx.x; e < GB * kHeadDim; e += 64 * nw) s_y[e] = L.y[uh0 * kHeadDim + e];
   __syncthreads();
 
   const float scale2 = L.scale * kLog2e;
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_contrib_kernel(BlocksL
   if (t + nw < ntile) step(T1, t + nw);
   __syncthreads();
   float *out = L.blocks + (int64_t)u * L.nblocks;
-  for (int64_t b = threadIdx.x; b < L.nblocks; b += blockDim.x) {
+  for (int64_t b = threadIdx.x; b < L.nblocks; b += 64 * nw) {
     float v = h0 == 0 ? 0.0f : out[b];
     for (int w = 0; w < nw; ++w) v += s_all[w * L.nblocks + b];
     out[b] = v;
@@ -291,31 +294,40 @@ size_t block_contrib_lds(int64_t nblocks, int gb, int waves) {
   return (size_t)(waves * nblocks + 16 + gb * kHeadDim) * sizeof(float);
 }
 
-// Waves per unit: enough for 2048 waves in the launch, at least two tiles each, and bins of at most
-// 64 KB together.
+// Waves per unit: eight, four of 257 to 512 units, at least two tiles each and bins of at most 64 KB
+// together.  More units fill the chip with a wave each; there the waves' bins and their sum only cost.
+// Units of 1540 rows, G = 4, 2048 blocks, us by 1 / 2 / 4 / 8 waves: 256 units 80 / 46 / 42 / 40, 300 84 / 57 / 62
+// / 65, 512 86 / 82 / 76 / 81, 600 93 / 105 / 99 / 108, 1000 144 / 144 / 142 / 154; 600 units, 8192 blocks
+// 110 / 146.
 int block_contrib_waves(const BlocksLaunch &L) {
-  int64_t w = 2048 / L.U;
+  int64_t w = L.U <= 256 ? kBlockWaves : L.U <= 512 ? kBlockWaves / 2 : 1;
   w = w < (L.max_rows + 31) / 32 ? w : (L.max_rows + 31) / 32;
   w = w < 16384 / L.nblocks ? w : 16384 / L.nblocks;
-  return (int)(w < 1 ? 1 : w > kBlockWaves ? kBlockWaves : w);
+  return (int)(w < 1 ? 1 : w);
+}
+
+template <bool SHARED>
+void launch_block_heads(const BlocksLaunch &L, int h0, int gb, int waves, hipStream_t s) {
+  const dim3 grid((unsigned)L.U), block(64 * waves);
+  const size_t lds = block_contrib_lds(L.nblocks, gb, waves);
+  switch (gb) {
+    case 1: hipLaunchKernelGGL((block_contrib_kernel<1, SHARED>), grid, block, lds, s, L, h0); break;
+    case 2: hipLaunchKernelGGL((block_contrib_kernel<2, SHARED>), grid, block, lds, s, L, h0); break;
+    case 3: hipLaunchKernelGGL((block_contrib_kernel<3, SHARED>), grid, block, lds, s, L, h0); break;
+    case 4: hipLaunchKernelGGL((block_contrib_kernel<4, SHARED>), grid, block, lds, s, L, h0); break;
+    case 5: hipLaunchKernelGGL((block_contrib_kernel<5, SHARED>), grid, block, lds, s, L, h0); break;
+    case 6: hipLaunchKernelGGL((block_contrib_kernel<6, SHARED>), grid, block, lds, s, L, h0); break;
+    case 7: hipLaunchKernelGGL((block_contrib_kernel<7, SHARED>), grid, block, lds, s, L, h0); break;
+    default: hipLaunchKernelGGL((block_contrib_kernel<8, SHARED>), grid, block, lds, s, L, h0); break;
+  }
 }
 
 hipError_t launch_block_contrib(const BlocksLaunch &L, hipStream_t s) {
   const int waves = block_contrib_waves(L);
-  const dim3 grid((unsigned)L.U), block(64 * waves);
   for (int h0 = 0; h0 < L.G; h0 += kHeadBlock) {
     const int gb = min(kHeadBlock, L.G - h0);
-    const size_t lds = block_contrib_lds(L.nblocks, gb, waves);
-    switch (gb) {
-      case 1: hipLaunchKernelGGL(block_contrib_kernel<1>, grid, block, lds, s, L, h0); break;
-      case 2: hipLaunchKernelGGL(block_contrib_kernel<2>, grid, block, lds, s, L, h0); break;
-      case 3: hipLaunchKernelGGL(block_contrib_kernel<3>, grid, block, lds, s, L, h0); break;
-      case 4: hipLaunchKernelGGL(block_contrib_kernel<4>, grid, block, lds, s, L, h0); break;
-      case 5: hipLaunchKernelGGL(block_contrib_kernel<5>, grid, block, lds, s, L, h0); break;
-      case 6: hipLaunchKernelGGL(block_contrib_kernel<6>, grid, block, lds, s, L, h0); break;
-      case 7: hipLaunchKernelGGL(block_contrib_kernel<7>, grid, block, lds, s, L, h0); break;
-      default: hipLaunchKernelGGL(block_contrib_kernel<8>, grid, block, lds, s, L, h0); break;
-    }
+    if (waves > 1) launch_block_heads<true>(L, h0, gb, waves, s);
+    else launch_block_heads<false>(L, h0, gb, 1, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -17,8 +17,12 @@ pytestmark = pytest.mark.gpu
     ([3000, 40], 1, 4096, 64),        # ... for four
     ([900, 700], 12, 64, 64),         # two head blocks
     ([700] * 3, 8, 1, 1 << 30),       # one block of everything
-    ([100 + u % 60 for u in range(700)], 2, 64, 64),    # two waves per unit
-    ([60 + u % 30 for u in range(2100)], 4, 64, 64),    # one
+    ([100 + u % 60 for u in range(700)], 2, 64, 64),    # a wave per unit
+    ([60 + u % 30 for u in range(2100)], 4, 64, 64),
+    ([100 + u % 90 for u in range(256)], 3, 64, 64),    # six waves per unit, the most of so short ones
+    ([100 + u % 90 for u in range(257)], 3, 64, 64),    # four from here
+    ([100 + u % 90 for u in range(512)], 5, 2048, 1),   # ... to here
+    ([100 + u % 90 for u in range(513)], 5, 8192, 1),   # a wave per unit, the most blocks
 ])
 def test_block_contributions_over_waves(sizes, G, nb, block_rows):
     print("block contributions over waves: %d units, longest %d, G=%d, %d blocks" % (len(sizes), max(sizes), G, nb), flush=True)
@@ -46,6 +50,7 @@ def test_block_contributions_over_waves(sizes, G, nb, block_rows):
                                     res["y"], res["lse"], blocks, block_rows=block_rows)
         outs.append(blocks)
     torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])  # each wave's bins are its own, summed in order
     got = outs[0].cpu().numpy().astype(np.float64)
     bits = synth.bf16_bits
     for u in sorted(set(np.linspace(0, U - 1, 12).astype(int))):
