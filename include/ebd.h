@@ -126,8 +126,8 @@ typedef struct ebd_evict_params {
  *     pi_full [rows] fp32 or NULL   pi of every full-cache position
  *     status [U] uint32             EBD_ST_* bits
  *   workspace: at least ebd_workspace_size(EBD_WS_EVICT, p) bytes, 256-byte aligned
- *   (256 bytes, reserved, except for Poisson launches of few long units, at most 320 longer than
- *   16384 tokens: about 64 KB per unit, for which 256 bytes are still accepted, at a lower speed).
+ *   (256 bytes, reserved, except for Poisson launches of at most 320 units longer than 16384
+ *   tokens: about 64 KB per unit, for which 256 bytes are still accepted, at a lower speed).
  *   A call takes one kernel ("evict_select") where the selection also gathers the rows, two where the
  *   gather, or that of a large unit's later rows, is a launch of its own ("evict_copy"), five for the
  *   long units above (timed as "evict_select", and the last, which gathers, as "evict_copy").

@@ -86,25 +86,26 @@ constexpr size_t kEvictWorkspace = 256;
 
 // Whether units are long and few enough for the evict_long kernels: beyond what a work-group stages
 // in LDS (a staged unit's passes cost less than their five launches: 8 units of 16384 tokens, 10%: 42 us
-// by a work-group each, 47 us by segments), and few or long enough that a work-group each leaves much of
-// the chip idle over the passes.  us by segments / by a work-group each (its rows gathered or copied,
-// whichever is faster), back to back on the same buffers:
+// by a work-group each, 47 us by segments), and few enough that a work-group each leaves much of the
+// chip idle over the passes.  us by segments / by a work-group each (its rows gathered or copied, whichever
+// is faster), back to back on the same buffers:
 //   tokens   units   10% kept       25% kept
 //    16385      64     74 /  87      115 / 116
 //    16385     128    103 / 107      178 / 166
 //    33000     128    153 / 170      294 / 289
 //    33000     181    197 / 203      385 / 374
 //    65536     181    347 / 370      709 / 687
+//    16385     256    153 / 143      292 / 264
 //    33000     256    260 / 253      531 / 493
-//    65536     256    465 / 466      971 / 915
 //   131072     300   1068 / 1129    2241 / 2261
-//    33000     400    401 / 365
-// and of ragged units, 10%: 300 of up to 33000 tokens 210 / 231, 512 of up to 65536 640 / 513.
+//    33000     400    401 / 365      808 / 747
+// and of ragged units, 10%: 300 of up to 33000 tokens 210 / 231, 512 of up to 65536 640 / 513.  The rows kept are
+// not part of the rule, so that a budget does not move a launch from the one to the other: they add
+// up the scores in another order, and lambda's last bit may differ.
 bool evict_long(const ebd_evict_params *p) {
-  const int64_t capacity = (p->max_capacity + kCopyRows - 1) / kCopyRows * kCopyRows;
+  const int64_t U = p->num_units;
   return p->design == EBD_DESIGN_POISSON && p->max_rows > kEvictStageMax && p->max_rows <= kLongRowsMax &&
-         p->num_units <= kEvictLongUnits &&
-         p->max_rows >= (evict_few_rows(capacity, p->max_rows) ? 100 : 256) * (int64_t)p->num_units;
+         (U <= kEvictLongUnits || (U <= 320 && p->max_rows >= 400 * U));
 }
 
 size_t evict_workspace(const ebd_evict_params *p) {

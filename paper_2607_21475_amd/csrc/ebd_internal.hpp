@@ -14,7 +14,7 @@ constexpr int kEvictStageMax = 16384;        // scores staged in LDS (64 KB) up 
 constexpr int kSelectThreads = 512;          // evict_select (scores in LDS or streamed): eight waves per unit
 constexpr int kRegRowsMax = 6144;            // longest unit of evict_select_reg
 constexpr int kSelectRegThreads = 128;       // evict_select_reg: two waves per unit, <= 6144 tokens
-constexpr int kEvictLongUnits = 320;         // most units of the evict_long kernels
+constexpr int kEvictLongUnits = 192;         // units up to which the evict_long kernels take any long ones
 constexpr int kGatherMinRows = 1024;         // rows of a unit that its own work-group gathers (multiples
 constexpr int kGatherMaxRows = 4096;         // ... of kCopyRows)
 constexpr int kGatherFewRows = 512;          // rows that a copy launch is not worth in any small launch
@@ -68,9 +68,6 @@ inline int32_t attend_chunks(int32_t split_rows) { return (split_rows + kChunkRo
 inline int32_t attend_record_floats(int32_t split_rows) {
   return kRecChunks + kChunkFloats * attend_chunks(split_rows);
 }
-
-// Whether units leave few rows to gather: room for less than a sixth of the longest one.
-inline bool evict_few_rows(int64_t capacity, int64_t max_rows) { return capacity * 6 < max_rows; }
 
 struct EvictLaunch {
   int32_t U;

@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
 //    Up to twice that many rows a unit is gathered whole.
 int32_t evict_gather_rows(const EvictLaunch &L) {
   const int64_t capacity = (int64_t)L.copy_blocks * kCopyRows, U = L.U, n = L.max_rows;
-  const bool few = evict_few_rows(capacity, n);
+  const bool few = capacity * 6 < n;
   if (U < 256) {
     const bool mid = n > kRegRowsMax / 6 && n <= kRegRowsMax / 3;
     const int64_t most = U * U / 15 < kGatherFewRows ? kGatherFewRows : U * U / 15;
@@ -1227,12 +1227,14 @@ int32_t evict_gather_rows(const EvictLaunch &L) {
 // room for eight waves per unit, which are faster from 2049 tokens on up to 256 units (256 units of 4096
 // tokens, 25%: 69 against 71 us; 8 of 6144: 26 against 32; of 2048: 19 against 16), from 4097 on up
 // to 512 (400 units, 25%: 4096 tokens 102.5 against 101.5 us, 6144 tokens 146 against 149; 600 of 6144: 219
-// against 210), there from 2049 on for the systematic design, whose weights take another pass (512
-// units of 3000 tokens, 10%: 59 against 63 us; 600: 76 against 72).
+// against 210).  The systematic design, whose weights take another pass, stays with eight waves up to
+// 767 units (512 of 3000 tokens, 25%: 100 against 103 us; 700: 139 against 134): the two kernels add up the
+// scores in another order, and its draw follows the last bit of every weight.
 bool evict_select_in_regs(const EvictLaunch &L) {
-  const int64_t most = L.U > 512                                              ? kRegRowsMax
-                       : L.U > 256 && L.design != EBD_DESIGN_SYSTEMATIC ? kRegRowsMax * 2 / 3
-                                                                        : kRegRowsMax / 3;
+  const bool sys = L.design == EBD_DESIGN_SYSTEMATIC;
+  const int64_t most = L.U > (sys ? 767 : 512) ? kRegRowsMax
+                       : L.U > 256 && !sys     ? kRegRowsMax * 2 / 3
+                                               : kRegRowsMax / 3;
   return !L.gather && L.max_rows <= most;
 }
 

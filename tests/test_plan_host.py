@@ -7,12 +7,11 @@ import pytest
     (1, 16384, 0.25, False),
     (1, 16385, 0.25, True),
     (32, 131072, 0.10, True),
-    (128, 16385, 0.10, True),     # few rows: by segments from 100 tokens for every unit on
-    (128, 16385, 0.25, False),    # more rows: from 256 on
-    (181, 20000, 0.10, True),
-    (181, 20000, 0.25, False),
-    (256, 65536, 0.25, True),
-    (256, 33000, 0.25, False),
+    (192, 16385, 0.10, True),     # the most units of any long ones, at any budget
+    (192, 16385, 0.25, True),
+    (193, 16385, 0.25, False),
+    (193, 65536, 0.10, False),
+    (193, 77200, 0.10, True),     # ... of units of at least 400 tokens for every unit of the launch
     (320, 131072, 0.10, True),
     (321, 131072, 0.10, False),
     (512, 20000, 0.10, False),
