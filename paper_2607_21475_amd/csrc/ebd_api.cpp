@@ -162,63 +162,103 @@ int64_t part_record_floats(int32_t rows, int32_t wpg) {
                  : attend_record_floats(rows);
 }
 
+// Whether a wave per unit, which finalizes all of the unit's heads together, beats waves that share it:
+// these combine their sums and finalize their heads one after the other, about 11 us a round, once per
+// generation of resident waves, and save less per 16 rows the fuller the last generation is, as
+// there the waves of other units keep the memory busy.  us by a wave each / by four (equal units; units of 10
+// to 100% of that budget):
+//   units  room     G = 4                     G = 8
+//     300   336     24 / 27                   25 / 38
+//     300   592     34 / 34;   34 / 30        35 / 44;   34 / 38
+//     300  1280     63 / 53                   65 / 64;   63 / 54
+//     680  1840     99 / 105;  88 / 79       102 / 123;  91 / 104
+//    1300   592     64 / 86;   40 / 66        65 / 118;  41 / 95
+//    1300  2496    262 / 256; 143 / 147      265 / 285; 146 / 181
+bool attend_wave_per_unit(int64_t U, int64_t cap, int gb) {
+  if (cap <= kWaveMinRows) return true;
+  if (cap > kSplitRowsLimit || attend_fused_lds_bytes((int32_t)cap, gb) > kSplitLdsBudget) return false;
+  const double tiles = (double)cap / 16.0;
+  if (U <= 256) return 0.58 * tiles < 6.5 - 0.5 * gb;  // eight waves each
+  const int64_t gens = (U * 4 + kResidentWaves - 1) / kResidentWaves;
+  const double fill = (double)(U * 4 - (gens - 1) * kResidentWaves) / kResidentWaves;
+  const double cost = 11.0 * (double)((gb + 3) / 4 * gens) + 0.5 * std::min(gb, 4) - 0.2 * gb - 5.3;
+  return tiles * (gens == 1 ? 0.3 : std::max(0.34 - 0.26 * fill, 0.215)) < cost;
+}
+
 // The workspace is sized by attend_split_rows (sr rows, ns splits); the launch uses at most that.
 //  * The caller's split_rows: one wave per split; up to eight splits share a work-group.
 //  * Many units (one split each): a wave per unit.
-//  * Otherwise a work-group of up to eight waves shares a unit, as many as keep 2048 waves resident
-//    (8 waves up to 256 units, 4 up to 512, 2 up to 1024 and above).  One work-group per unit
-//    needs no record and no second launch, but its waves read 16 rows in about 1.3 us, so launches of
-//    fewer than 256 units cut theirs into parts until 256 work-groups run, at least 96 rows per
-//    wave: 8 units of 2070 rows, G = 4: 44.6 us whole, 35.3 us in parts; 64 ragged units of up to 3000
-//    rows, G = 7: 57.6 and 40.1 us; 128 units of 2140 rows: 49.6 and 46.6 us; one part (1025 rows): 32.4 us.
-//    Short units are quicker by a wave each (the estimate below), above all where a work-group has
-//    fewer waves than heads: 755 units of up to 400 rows, G = 8: 66 us shared, 35 us by a wave each;
-//    527 of up to 340 rows, G = 3: 42 and 31 us; 260 of 100 rows, G = 2: 19.4 and 16.5 us; 1286 of up to
-//    960 rows, G = 6: 132 and 90 us; 1100 of 1800 rows, G = 8: 258 and 201 us (from 2560 rows on two
-//    waves win there: 1124 ragged units of up to 3600 rows 275 and 282 us).
-//  * Long units whose work-groups would leave the chip a quarter empty or more (257 to 383 units of
-//    four waves, 513 to 767 of two) and those whose LDS would not fit: one-wave splits with records.
-//    260 units of 7040 rows, G = 12, without offset: 1015 us shared, 778 us by splits; 372 ragged units
-//    of up to 4100 rows, G = 6: 143 and 121 us.
+//  * Otherwise the waves of a work-group share a unit: one work-group per unit needs no record and no
+//    second launch, and where lengths differ a shorter unit's rows are dealt over all of its waves.
+//    Eight waves up to 256 units, four above, eight again where four would need more LDS than half a
+//    CU's (3000 units of 14352 rows, G = 8: 3250 us, one-wave splits with records 3803; but 384 units of 17000
+//    rows 637 and 586, so up to 16384 rows).
+//  * One work-group's waves read 16 rows in about 1.3 us, so launches of fewer than 256 units cut theirs
+//    into parts with records until 256 work-groups run, at least 96 rows per wave: 8 units of 2070
+//    rows, G = 4: 44.6 us whole, 35.3 us in parts; 64 ragged units of up to 3000 rows, G = 7: 57.6 and 40.1
+//    us; 128 units of 2140 rows: 49.6 and 46.6 us; one part (1025 rows): 32.4 us.
+// The exceptions, each with us for (equal units | units of 10 to 100% of that budget), the host not
+// knowing which:
+//  * Short units, a wave each (attend_wave_per_unit below).
+//  * 129 to 199 units past 4096 rows leave up to half of the chip without a work-group, and its waves
+//    without a second one: one-wave splits (180 of 9776, G = 4: shared 167 | 149, splits 170 | 111).
+//  * 200 to 256 units past 12288 rows (16384 for more than four heads): three parts of four waves whose
+//    rows are not dealt out, so that a short unit's later parts end at once (225 of 21152, G = 4: shared
+//    379 | 317, splits 427 | 268, three parts 425 | 253; of 14352: 259 | 219, 296 | 188, 297 | 179).
+//  * 257 to 383 units of five or six splits leave a quarter of the chip empty with four waves each, which
+//    the splits fill (300 of 2496, G = 4: shared 90 | 68, splits 84 | 60).
+//  * Up to 1024 units of two splits, from 768 on for one head, 897 for four, never for eight: their waves
+//    are all resident at once, where four each take a second round (900 of 3456, G = 1: four 234 | 143,
+//    two 238 | 127; 1024 of 6640, G = 4: 493 | 290 and 496 | 259, G = 8: 505 | 321 and 648 | 400).
+//  * Past 32768 rows, and past 16384 with more than 512 units, one-wave splits: the launch ends with its last
+//    long unit (1024 units, one in 16 of 41616 rows and the others an eighth of that, G = 4: shared by eight
+//    waves 2336, splits 857).
 AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
   const int64_t cap = (int64_t)ns * sr, U = p->num_units;  // every plan covers the same rows
   const int gb = std::min(p->group, kHeadBlock);
+  const AttendPlan splits = {ns, 1, sr, 0}, whole = {1, 1, (int32_t)std::min<int64_t>(cap, INT32_MAX), 0};
   if (p->split_rows > 0) {
     if (ns > 1 && ns <= kUnitWaves && attend_shared_lds_bytes(sr, ns, gb, false) <= kUnitLdsMax)
       return {1, ns, sr, 0};
-    return {ns, 1, sr, 0};
+    return splits;
   }
-  if (U * ((p->group + kHeadBlock - 1) / kHeadBlock) >= kSplitWaves && ns == 1) return {1, 1, sr, 0};
-  if (cap <= kWaveMinRows) return {1, 1, sr, 0};
-  const int32_t wpg = U <= 256 ? 8 : U <= 512 ? 4 : 2;
-  const size_t lds_max = kUnitLdsMax * (size_t)wpg / kUnitWaves;  // so that 8 waves share a CU
-  if (cap <= (U > 1024 ? kWholeRowsMany : kSplitRowsLimit) &&
-      attend_fused_lds_bytes((int32_t)cap, gb) <= kSplitLdsBudget) {
-    // us: 16 rows take a wave 0.75 us, 1.35 us with another one on its SIMD; a shared unit's waves
-    // combine their sums and finalize their heads one after the other, 11 us each, a lone wave all
-    // its heads together
-    const double tiles = (double)cap / 16.0;
-    const double shared = tiles / wpg * 1.35 * std::ceil((double)U * wpg / kResidentWaves) + 6.0 +
-                          11.0 * ((gb + wpg - 1) / wpg);
-    const double whole = tiles * (U > 1024 ? 1.35 : 0.75) + 10.5 + 0.5 * gb;
-    if (whole < shared) return {1, 1, (int32_t)((cap + 15) / 16 * 16), 0};
-  }
-  if (U > 256 && U * wpg < kSplitWaves && cap > kLongRows) return {ns, 1, sr, 0};
-  int64_t parts = 1;
-  if (U < 256) parts = std::max<int64_t>(1, std::min<int64_t>(256 / U, cap / (kPartWaveRows * wpg)));
+  if (U * ((p->group + kHeadBlock - 1) / kHeadBlock) >= kSplitWaves && ns == 1) return whole;
+  if (attend_wave_per_unit(U, cap, gb)) return whole;
+
+  // rows of each of `waves` waves; whether `parts` parts of wpg waves fit `lds`, and the workspace
+  auto rows_of = [&](int64_t waves) { return (int32_t)(((cap + waves - 1) / waves + 15) / 16 * 16); };
+  auto fits = [&](int64_t parts, int32_t wpg, size_t lds) {
+    const int32_t rows = rows_of(parts * wpg);
+    return rows <= kSplitRowsLimit && attend_shared_lds_bytes(rows, wpg, gb, parts > 1) <= lds;
+  };
   const int64_t room = (int64_t)ns * attend_record_floats(sr);  // per (unit, head)
+  auto recorded = [&](int64_t parts, int32_t wpg) {
+    return parts == 1 || parts * part_record_floats(rows_of(parts * wpg), wpg) <= room;
+  };
+  if (U > 256) {
+    if (U < 384 && ns >= 5) return splits;
+    if (cap > (U > 512 ? 16384 : 32768)) return splits;
+    if (U >= 725 + 43 * gb && U <= 1024 && ns == 2 &&
+        attend_shared_lds_bytes(sr, 2, gb, false) <= kUnitLdsMax / 4)
+      return {1, 2, sr, 0};
+    if (fits(1, 4, kUnitLdsMax / 2)) return {1, 4, std::max(rows_of(4), kWaveMinRows), 1};
+    if (cap <= 16384 && fits(1, 8, kUnitLdsMax)) return {1, 8, std::max(rows_of(8), kWaveMinRows), 1};
+    return splits;
+  }
+  if (U > 128 && U < 200 && cap > 4096) return splits;
+  if (U >= 200 && cap > (gb > 4 ? 16384 : 12288)) {
+    for (int32_t parts = 3; parts <= 4; ++parts)
+      if (fits(parts, 4, kUnitLdsMax / 2) && recorded(parts, 4)) return {parts, 4, rows_of(parts * 4), 0};
+    return splits;
+  }
   // fewest parts that the LDS allows, at least the wanted ones, then fewer while records exceed
   // the workspace
-  auto rows_of = [&](int64_t n) { return (int32_t)(((cap + n * wpg - 1) / (n * wpg) + 15) / 16 * 16); };
-  while (parts < kMaxSplits && (rows_of(parts) > kSplitRowsLimit ||
-                                attend_shared_lds_bytes(rows_of(parts), wpg, gb, parts > 1) > lds_max))
-    ++parts;
-  while (parts > 1 && parts * part_record_floats(rows_of(parts), wpg) > room) --parts;
-  const int32_t rows = rows_of(parts);
-  if (parts > 1 && U > 256) return {ns, 1, sr, 0};  // more waves than the chip holds: one-wave splits
-  if (rows > kSplitRowsLimit || attend_shared_lds_bytes(rows, wpg, gb, parts > 1) > lds_max || parts >= kMaxSplits)
-    return {ns, 1, sr, 0};  // records of one-wave splits
-  return {(int32_t)parts, wpg, std::max(rows, kWaveMinRows), 1};
+  int64_t parts = 1;
+  if (U < 256) parts = std::max<int64_t>(1, std::min<int64_t>(256 / U, cap / (kPartWaveRows * kUnitWaves)));
+  while (parts < kMaxSplits && !fits(parts, kUnitWaves, kUnitLdsMax)) ++parts;
+  while (parts > 1 && !recorded(parts, kUnitWaves)) --parts;
+  if (parts >= kMaxSplits || !fits(parts, kUnitWaves, kUnitLdsMax)) return splits;
+  return {(int32_t)parts, kUnitWaves, std::max(rows_of(parts * kUnitWaves), kWaveMinRows), 1};
 }
 
 // Rows per scores split: as for attention, one split per unit when the units give enough

@@ -29,11 +29,9 @@ constexpr int kSplitMaxRows = 4096;  // default split length cap (bounds the lau
 constexpr int kSplitMinRows = 256;   // default split length floor
 constexpr int kSplitWaves = 1536;    // default: cut units until the launch has this many waves
 constexpr int kSplitRowsLimit = 8192;  // largest split a caller may ask for (LDS of one wave)
-constexpr int kMaxSplits = 4096;       // splits per unit (the finalize keeps a scale per split and head in LDS)
+constexpr int kMaxSplits = 4096;       // splits per unit; a layout that needs more is refused
 constexpr int kUnitWaves = 8;          // most waves of a work-group that shares a unit (two per SIMD)
 constexpr size_t kUnitLdsMax = 155648;  // LDS of such a work-group of 8 waves, alone on its CU (of 160 KB)
-constexpr int kWholeRowsMany = 2560;   // longest unit of a wave of its own in launches of 1025 to 1535 units
-constexpr int kLongRows = 2048;        // from here records cost less than a quarter of the chip left empty
 constexpr int kWaveMinRows = 32;       // fewest rows worth a wave of its own
 constexpr int kPartWaveRows = 96;      // ... when a unit is cut into parts with records
 constexpr size_t kSplitLdsBudget = 20480;  // LDS of one split wave at two waves per SIMD (160 KB / 8)

@@ -1,6 +1,5 @@
 """GPU parity of certified attention where the library cuts the launch itself: a work-group of
-several waves per unit (8, 4 or 2 of them by the number of units), long units of small launches in
-several parts whose records a second kernel combines, and one wave per unit in large launches.
+several waves per unit (8, 4 or 2 of them), long units of small launches in several parts whose records a second kernel combines, and one wave per unit in large launches.
 The oracle and the bars are those of test_gpu_parity."""
 import numpy as np
 import pytest
@@ -56,10 +55,10 @@ def _units(sizes, G, seed, dominant=0):
     ([70000, 1], 1, 0),
     ([3700] * 200, 4, 0),                          # more units than would leave room for parts
     ([600 + 7 * (u % 50) for u in range(300)], 4, 2),     # four waves per unit
-    ([300 + 5 * (u % 50) for u in range(600)], 7, 0),     # two waves per unit
+    ([300 + 5 * (u % 50) for u in range(600)], 7, 0),     # a wave per unit
     ([1100] * 520 + [0] * 3, 8, 0),
     ([64 + u % 40 for u in range(1540)], 4, 0),    # a wave per unit
-    ([2700] * 1536, 8, 0),                         # ... whose LDS would not hold it: two waves
+    ([2700] * 1536, 8, 0),                         # ... whose LDS would not hold it: four waves
 ])
 def test_attend_library_plans(sizes, G, dominant):
     _say("attend plans units=%d longest=%d G=%d dominant=%d" % (len(sizes), max(sizes), G, dominant))
@@ -92,6 +91,27 @@ def test_attend_library_plans(sizes, G, dominant):
         v = bf16_to_f64(_bits(rc.Vc[j:j + 1]))[0]
         y = _np(res["y"][u, 0]).astype(np.float64)
         assert np.linalg.norm(y - v) < 0.2 * np.linalg.norm(v)
+
+
+@pytest.mark.parametrize("sizes,G,dominant", [
+    ([5000, 4097, 100, 0] + [16] * 146, 7, 3),      # 129 to 199 units: one-wave splits
+    ([13000, 12400, 4400, 300] + [16] * 206, 4, 5),  # 200 to 256: three parts, rows not dealt out
+    ([17000, 8500] + [16] * 254, 8, 9),
+    ([1400, 300] + [16] * 298, 4, 2),               # 257 to 383: five one-wave splits
+    ([1400, 300] + [16] * 382, 4, 2),               # four waves from 384 on
+    ([3000, 2999, 17] + [40] * 530, 4, 4),          # ... also of more than 512 units
+    ([1900, 700] + [40] * 511, 8, 2),
+    ([13400, 9000] + [16] * 520, 8, 3),             # eight: the LDS of four would be too much
+    ([3000, 1600] + [40] * 800, 1, 3),              # two waves each, all of them resident
+    ([2500, 1200] + [40] * 900, 4, 3),
+    ([1900, 1300] + [40] * 900, 8, 2),              # a wave per unit
+    ([33000, 100] + [16] * 300, 2, 9),              # the longest: one-wave splits
+    ([16500, 100] + [16] * 520, 3, 9),
+])
+def test_attend_library_plans_of_many_units(sizes, G, dominant):
+    """The plans of more than 128 units, on both sides of their lines; the host knows the longest unit only,
+    so the others are short."""
+    test_attend_library_plans(sizes, G, dominant)
 
 
 @pytest.mark.parametrize("sizes,G", [([13100] * 2, 4), ([600] * 5, 7)])

@@ -1,5 +1,6 @@
 """Which kernels a call launches, on both sides of the lines of the dispatch (timed with the library's own
-record): the eviction's gather as a launch of its own or by the selection."""
+record): the eviction's gather as a launch of its own or by the selection, and attention with or without
+records for a finalize."""
 import pytest
 import torch
 
@@ -59,3 +60,42 @@ def test_evict_gather_launches(units, n, budget, design, copies):
     got = _launches(("evict_select", "evict_copy"),
                     lambda: ebd.ebd_evict(p, sc, K, V, Kc, Vc, pic, idx, cnt, st, ws))
     assert got == (1, copies)
+
+
+@pytest.mark.parametrize("units,n,G,finalizes", [
+    (129, 4000, 4, 0),      # waves that share a unit
+    (129, 4200, 4, 1),      # 129 to 199 units past 4096 rows: splits with records
+    (199, 4200, 4, 1),
+    (200, 4200, 4, 0),
+    (256, 12000, 4, 0),
+    (256, 13000, 4, 1),     # 200 to 256 past 12288 rows: parts
+    (256, 13000, 8, 0),     # ... past 16384 for more heads
+    (256, 17000, 8, 1),
+    (257, 1000, 4, 0),      # 257 to 383 of five or six splits: records
+    (257, 1300, 4, 1),
+    (383, 1300, 4, 1),
+    (384, 1300, 4, 0),
+    (512, 30000, 4, 0),
+    (512, 33000, 4, 1),     # the longest
+    (513, 16000, 4, 0),
+    (513, 17000, 4, 1),
+    (1535, 13400, 8, 0),    # eight waves, whose LDS fits where that of four does not
+    (1536, 9000, 8, 0),
+    (1536, 17000, 1, 1),
+])
+def test_attend_launches(units, n, G, finalizes):
+    _say("attend launches units=%d n=%d G=%d" % (units, n, G))
+    import paper_2607_21475_amd as ebd
+
+    # every unit is empty: only the launches are looked at
+    off = torch.zeros(units + 1, dtype=torch.int64, device="cuda")
+    cnt = torch.zeros(units, dtype=torch.int32, device="cuda")
+    K, V = (torch.zeros((16, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q, pi = torch.zeros((units, G, 128), dtype=torch.bfloat16, device="cuda"), torch.zeros(16, device="cuda")
+    y, vhat, lse = torch.empty((units, G, 128), device="cuda"), *torch.empty((2, units, G), device="cuda")
+    p = ebd.attend_params(units, G, n, off)
+    ws = ebd.workspace(ebd.ebd_workspace_size(ebd.EBD_WS_ATTEND, p))
+    got = _launches(("attend_split", "attend_finalize"),
+                    lambda: ebd.ebd_attend_certify(p, q, K, V, pi, cnt, y, vhat, lse, ws))
+    assert got == (1, finalizes)
+    assert not y.any() and torch.all(torch.isneginf(lse))
