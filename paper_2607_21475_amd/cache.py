@@ -160,8 +160,8 @@ def direct_variances(ws: torch.Tensor, num_units: int, group: int) -> int:
 
 
 def uses_split_records(ws_bytes: int, num_units: int, group: int) -> bool:
-    """Whether an attention launch planned with this workspace size cuts units into several
-    splits whose partial records go through the workspace (otherwise it holds only the
-    diagnostic counts)."""
+    """Whether this attention workspace has room for units' partial records (otherwise it holds only
+    the diagnostic counts).  A launch may still need none: waves of one work-group that share a unit
+    combine their sums in LDS."""
     nhb = (int(group) + 7) // 8
     return ws_bytes > (8 * num_units * nhb + 255) // 256 * 256

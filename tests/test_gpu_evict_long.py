@@ -82,7 +82,9 @@ def test_evict_long_parity(lengths, kind, budget, eps, mode):
     with np.errstate(invalid="ignore"):  # +inf where nothing is evicted
         same = (lam == rlam) | (np.abs(lam - rlam) <= 3e-7 * np.abs(rlam))
     assert np.all(same), (lam, rlam)
-    for u in np.nonzero(lam == rlam)[0]:
+    equal = [u for u in np.nonzero(lam == rlam)[0] if lengths[u] > 0]
+    assert equal  # the orders of summation differ far below an ulp of fp32: some unit has the same bits
+    for u in equal:
         n = int(ref["count"][u])
         assert n == int(out.count[u])
         for k in ("Kc", "Vc", "pic", "idxc"):
@@ -129,11 +131,13 @@ def test_evict_long_layout_overflow_and_replay():
     with torch.cuda.stream(s):
         with torch.cuda.graph(g, stream=s):
             call()
-    for _ in range(3):
+    first.update(count=count.clone(), status=st.clone(), lam=lam.clone())
+    for _ in range(3):  # over sentinels everywhere: what the call wrote is written again, the rest is left
         for v in o.values():
-            v[:n0] = 0
+            v.fill_(7)
+        count.fill_(-1), st.fill_(-1), lam.fill_(7.0)
         ws.fill_(255)
         g.replay()
         torch.cuda.synchronize()
-        for k, v in o.items():
+        for k, v in dict(o, count=count, status=st, lam=lam).items():
             assert torch.equal(v, first[k]), k

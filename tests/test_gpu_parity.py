@@ -109,11 +109,12 @@ def _check_evict(lengths, K, V, seq_off, sc, out, n_sink=4, n_recent=64, budget=
     ([6144] * 6, 0.25),                       # 3 chunks per unit
     ([0, 1, 5, 70, 100, 777, 2047, 2048, 2049, 4096, 5000, 6144, 9000, 16384], 0.2),  # ragged
     ([20000, 40001, 3], 0.1),                 # longer than 16384: streamed scores
-    # units of at most 6144 tokens: scores held in registers, 2 to 12 groups per thread
+    # shorter ones; few units of at most 2048 tokens hold their scores in registers (test_gpu_evict_regs
+    # has the longer ones of large launches)
     ([0, 1, 5, 70, 100, 777, 2047, 2048, 2049, 4096, 5000, 6144], 0.2),
     ([1, 3, 511, 512, 513, 1024], 0.3),
     ([2000, 17, 1500], 0.15),
-    ([3000, 4096, 2500, 100, 2049], 0.3),     # 8 groups per thread
+    ([3000, 4096, 2500, 100, 2049], 0.3),
 ])
 def test_evict_parity(lengths, budget):
     _say("evict parity lengths=%s budget=%s" % (lengths[:6], budget))
@@ -225,8 +226,8 @@ def test_evict_deterministic():
     ([4096] * 8, 0.10),
     ([0, 1, 5, 70, 100, 777, 2047, 2048, 2049, 5000, 16384], 0.25),
     ([20000, 40001, 3], 0.1),                 # streamed scores
-    ([0, 1, 5, 70, 777, 2049, 5000, 6144], 0.25),   # scores in registers
-    ([1024, 9], 0.2),
+    ([0, 1, 5, 70, 777, 2049, 5000, 6144], 0.25),
+    ([1024, 9], 0.2),                         # scores in registers
 ])
 def test_evict_systematic_design(lengths, budget):
     _say("evict systematic lengths=%s budget=%s" % (lengths[:6], budget))
@@ -248,8 +249,8 @@ def test_evict_systematic_design(lengths, budget):
     ([0, 1, 5, 70, 777, 2048, 5000, 16384], 0.3, True),   # integer scores: many ties
     ([20000, 40001, 3], 0.1, True),                       # streamed scores
     ([3000, 3000], 1.0, False),                           # k = |T|: keep everything
-    ([0, 1, 5, 70, 777, 2048, 5000, 6144], 0.3, True),    # scores in registers
-    ([900, 1024], 0.05, False),
+    ([0, 1, 5, 70, 777, 2048, 5000, 6144], 0.3, True),
+    ([900, 1024], 0.05, False),                           # a few rows, gathered by the selection
 ])
 def test_evict_topk_design(lengths, budget, ties):
     _say("evict top-k lengths=%s budget=%s ties=%s" % (lengths[:6], budget, ties))
@@ -277,7 +278,7 @@ def test_evict_topk_design(lengths, budget, ties):
 
 @pytest.mark.parametrize("lengths", [
     [4096, 333, 6144, 20000],   # streamed scores
-    [4096, 333, 6144],          # scores in registers
+    [4096, 333, 6144],          # scores staged
 ])
 def test_evict_uniform_design(lengths):
     _say("evict uniform lengths=%s" % lengths)
