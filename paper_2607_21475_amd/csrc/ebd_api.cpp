@@ -210,6 +210,9 @@ bool attend_wave_per_unit(int64_t U, int64_t cap, int gb) {
 //  * Up to 1024 units of two splits, from 768 on for one head, 897 for four, never for eight: their waves
 //    are all resident at once, where four each take a second round (900 of 3456, G = 1: four 234 | 143,
 //    two 238 | 127; 1024 of 6640, G = 4: 493 | 290 and 496 | 259, G = 8: 505 | 321 and 648 | 400).
+//  * Tens of thousands of units, most of them far shorter than the longest: two waves each, with their rows
+//    dealt out (units of 170 to 8250 rows, G = 1: 12096 of them four 1799, two 1843; 48384 four 6917, two
+//    6772).
 //  * Past 32768 rows, and past 16384 with more than 512 units, one-wave splits: the launch ends with its last
 //    long unit (1024 units, one in 16 of 41616 rows and the others an eighth of that, G = 4: shared by eight
 //    waves 2336, splits 857).
@@ -241,6 +244,7 @@ AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
     if (U >= 725 + 43 * gb && U <= 1024 && ns == 2 &&
         attend_shared_lds_bytes(sr, 2, gb, false) <= kUnitLdsMax / 4)
       return {1, 2, sr, 0};
+    if (U > 24576 && fits(1, 2, kUnitLdsMax / 4)) return {1, 2, std::max(rows_of(2), kWaveMinRows), 1};
     if (fits(1, 4, kUnitLdsMax / 2)) return {1, 4, std::max(rows_of(4), kWaveMinRows), 1};
     if (cap <= 16384 && fits(1, 8, kUnitLdsMax)) return {1, 8, std::max(rows_of(8), kWaveMinRows), 1};
     return splits;

@@ -95,6 +95,7 @@ def test_attend_library_plans(sizes, G, dominant):
 
 @pytest.mark.parametrize("sizes,G,dominant", [
     ([5000, 4097, 100, 0] + [16] * 146, 7, 3),      # 129 to 199 units: one-wave splits
+    ([5000, 4097, 100, 0] + [16] * 146, 6, 0),
     ([13000, 12400, 4400, 300] + [16] * 206, 4, 5),  # 200 to 256: three parts, rows not dealt out
     ([17000, 8500] + [16] * 254, 8, 9),
     ([1400, 300] + [16] * 298, 4, 2),               # 257 to 383: five one-wave splits
@@ -107,6 +108,7 @@ def test_attend_library_plans(sizes, G, dominant):
     ([1900, 1300] + [40] * 900, 8, 2),              # a wave per unit
     ([33000, 100] + [16] * 300, 2, 9),              # the longest: one-wave splits
     ([16500, 100] + [16] * 520, 3, 9),
+    ([9000, 5000, 300] + [16] * 24600, 1, 6),       # two waves each of the most units
 ])
 def test_attend_library_plans_of_many_units(sizes, G, dominant):
     """The plans of more than 128 units, on both sides of their lines; the host knows the longest unit only,

@@ -23,6 +23,10 @@ pytestmark = pytest.mark.gpu
     ([100 + u % 90 for u in range(257)], 3, 64, 64),    # four from here
     ([100 + u % 90 for u in range(512)], 5, 2048, 1),   # ... to here
     ([100 + u % 90 for u in range(513)], 5, 8192, 1),   # a wave per unit, the most blocks
+    ([20 + u % 30 for u in range(520)], 1, 16, 4),
+    ([20 + u % 30 for u in range(520)], 3, 16, 4),
+    ([20 + u % 30 for u in range(520)], 6, 16, 4),
+    ([20 + u % 30 for u in range(520)], 8, 16, 4),
 ])
 def test_block_contributions_over_waves(sizes, G, nb, block_rows):
     print("block contributions over waves: %d units, longest %d, G=%d, %d blocks" % (len(sizes), max(sizes), G, nb), flush=True)
