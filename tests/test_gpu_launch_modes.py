@@ -43,7 +43,7 @@ def test_evict_gather_launches(units, n, budget, design, copies):
     import paper_2607_21475_amd as ebd
     from paper_2607_21475_amd import cache
 
-    # every unit reads the same rows of one cache: only the launches are looked at
+    # one unit holds rows, the others are empty: only the launches are looked at
     g = torch.Generator(device="cuda").manual_seed(1)
     K, V = (torch.randn((n, 128), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
     sc = torch.rand(n, generator=g, device="cuda")
