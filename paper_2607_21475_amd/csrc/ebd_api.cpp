@@ -190,9 +190,10 @@ bool attend_wave_per_unit(int64_t U, int64_t cap, int gb) {
 //  * Many units (one split each): a wave per unit.
 //  * Otherwise the waves of a work-group share a unit: one work-group per unit needs no record and no
 //    second launch, and where lengths differ a shorter unit's rows are dealt over all of its waves.
-//    Eight waves up to 256 units, four above, eight again where four would need more LDS than half a
-//    CU's (3000 units of 14352 rows, G = 8: 3250 us, one-wave splits with records 3803; but 384 units of 17000
-//    rows 637 and 586, so up to 16384 rows).
+//    Every wave takes an equal share, which also keeps its sums short.  Eight waves up to 256 units, four
+//    above, eight again where four would need more LDS than half a CU's (3000 units of 14352 rows, G = 8:
+//    3250 us, one-wave splits with records 3803; but 384 units of 17000 rows 637 and 586, so up to 16384
+//    rows).
 //  * One work-group's waves read 16 rows in about 1.3 us, so launches of fewer than 256 units cut theirs
 //    into parts with records until 256 work-groups run, at least 96 rows per wave: 8 units of 2070
 //    rows, G = 4: 44.6 us whole, 35.3 us in parts; 64 ragged units of up to 3000 rows, G = 7: 57.6 and 40.1
@@ -200,16 +201,16 @@ bool attend_wave_per_unit(int64_t U, int64_t cap, int gb) {
 // The exceptions, each with us for (equal units | units of 10 to 100% of that budget), the host not
 // knowing which:
 //  * Short units, a wave each (attend_wave_per_unit below).
-//  * 129 to 199 units past 4096 rows leave up to half of the chip without a work-group, and its waves
-//    without a second one: one-wave splits (180 of 9776, G = 4: shared 167 | 149, splits 170 | 111).
-//  * 200 to 256 units past 12288 rows (16384 for more than four heads): three parts of four waves whose
-//    rows are not dealt out, so that a short unit's later parts end at once (225 of 21152, G = 4: shared
-//    379 | 317, splits 427 | 268, three parts 425 | 253; of 14352: 259 | 219, 296 | 188, 297 | 179).
+//  * 129 to 180 units past 4096 rows, up to 256 of up to four heads past 12288: a work-group each leaves up to
+//    half of the chip empty, or waits for the longest unit, so three parts of four waves each, four past
+//    12288 rows (160 of 9776, G = 4: whole 163 | 148, three 140 | 117; 180 of 14352: whole 239 | 213, four 227 |
+//    148; 225 of 14352: 259 | 219, 296 | 189; but 200 of 9776: 172 | 152, three 191 | 137).
 //  * 257 to 383 units of five or six splits leave a quarter of the chip empty with four waves each, which
 //    the splits fill (300 of 2496, G = 4: shared 90 | 68, splits 84 | 60).
-//  * Up to 1024 units of two splits, from 768 on for one head, 897 for four, never for eight: their waves
-//    are all resident at once, where four each take a second round (900 of 3456, G = 1: four 234 | 143,
-//    two 238 | 127; 1024 of 6640, G = 4: 493 | 290 and 496 | 259, G = 8: 505 | 321 and 648 | 400).
+//  * 896 to 1024 units of one or two heads, and 768 to 895 short ones; 960 to 1024 long ones of up to four: two
+//    waves each are all resident at once, where four take a second round for little (1000 of 2496, G = 1:
+//    four 177 | 114, two 177 | 101; 1024 of 14352, G = 4: 1059 | 625, 1067 | 580).  With more heads the second
+//    round pays, as the waves share the finalizes (1024 of 6640, G = 8: 505 | 321, two 645 | 379).
 //  * Tens of thousands of units, most of them far shorter than the longest: two waves each, with their rows
 //    dealt out (units of 170 to 8250 rows, G = 1: 12096 of them four 1799, two 1843; 48384 four 6917, two
 //    6772).
@@ -241,20 +242,16 @@ AttendPlan attend_plan(const ebd_attend_params *p, int32_t sr, int32_t ns) {
   if (U > 256) {
     if (U < 384 && ns >= 5) return splits;
     if (cap > (U > 512 ? 16384 : 32768)) return splits;
-    if (U >= 725 + 43 * gb && U <= 1024 && ns == 2 &&
-        attend_shared_lds_bytes(sr, 2, gb, false) <= kUnitLdsMax / 4)
-      return {1, 2, sr, 0};
-    if (U > 24576 && fits(1, 2, kUnitLdsMax / 4)) return {1, 2, std::max(rows_of(2), kWaveMinRows), 1};
+    const bool two = gb <= 2 ? U >= (cap > 2496 ? 896 : 768) : gb <= 4 && U >= 960 && cap > 3072;
+    if (((two && U <= 1024) || U > 24576) && fits(1, 2, kUnitLdsMax / 4))
+      return {1, 2, std::max(rows_of(2), kWaveMinRows), 1};
     if (fits(1, 4, kUnitLdsMax / 2)) return {1, 4, std::max(rows_of(4), kWaveMinRows), 1};
     if (cap <= 16384 && fits(1, 8, kUnitLdsMax)) return {1, 8, std::max(rows_of(8), kWaveMinRows), 1};
     return splits;
   }
-  if (U > 128 && U < 200 && cap > 4096) return splits;
-  if (U >= 200 && cap > (gb > 4 ? 16384 : 12288)) {
-    for (int32_t parts = 3; parts <= 4; ++parts)
-      if (fits(parts, 4, kUnitLdsMax / 2) && recorded(parts, 4)) return {parts, 4, rows_of(parts * 4), 0};
-    return splits;
-  }
+  if (U > 128 && (U <= 180 ? cap > 4096 : gb <= 4 && cap > 12288))
+    for (int32_t parts = cap > 12288 ? 4 : 3; parts >= 3; --parts)
+      if (fits(parts, 4, kUnitLdsMax / 2) && recorded(parts, 4)) return {parts, 4, rows_of(parts * 4), 1};
   // fewest parts that the LDS allows, at least the wanted ones, then fewer while records exceed
   // the workspace
   int64_t parts = 1;

@@ -94,17 +94,19 @@ def test_attend_library_plans(sizes, G, dominant):
 
 
 @pytest.mark.parametrize("sizes,G,dominant", [
-    ([5000, 4097, 100, 0] + [16] * 146, 7, 3),      # 129 to 199 units: one-wave splits
+    ([5000, 4097, 100, 0] + [16] * 146, 7, 3),      # 129 to 199 units: three parts of four waves
     ([5000, 4097, 100, 0] + [16] * 146, 6, 0),
-    ([13000, 12400, 4400, 300] + [16] * 206, 4, 5),  # 200 to 256: three parts, rows not dealt out
+    ([13000, 12400, 4400, 300] + [16] * 206, 4, 5),  # ... or four; 200 to 256 longer ones too
     ([17000, 8500] + [16] * 254, 8, 9),
     ([1400, 300] + [16] * 298, 4, 2),               # 257 to 383: five one-wave splits
     ([1400, 300] + [16] * 382, 4, 2),               # four waves from 384 on
     ([3000, 2999, 17] + [40] * 530, 4, 4),          # ... also of more than 512 units
     ([1900, 700] + [40] * 511, 8, 2),
     ([13400, 9000] + [16] * 520, 8, 3),             # eight: the LDS of four would be too much
-    ([3000, 1600] + [40] * 800, 1, 3),              # two waves each, all of them resident
-    ([2500, 1200] + [40] * 900, 4, 3),
+    ([3000, 1600] + [40] * 900, 1, 3),              # two waves each, all of them resident
+    ([2400, 1600] + [40] * 770, 2, 3),
+    ([3500, 1200] + [40] * 960, 4, 3),
+    ([2500, 1200] + [40] * 960, 4, 3),              # four
     ([1900, 1300] + [40] * 900, 8, 2),              # a wave per unit
     ([33000, 100] + [16] * 300, 2, 9),              # the longest: one-wave splits
     ([16500, 100] + [16] * 520, 3, 9),

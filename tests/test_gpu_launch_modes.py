@@ -64,13 +64,12 @@ def test_evict_gather_launches(units, n, budget, design, copies):
 
 @pytest.mark.parametrize("units,n,G,finalizes", [
     (129, 4000, 4, 0),      # waves that share a unit
-    (129, 4200, 4, 1),      # 129 to 199 units past 4096 rows: splits with records
-    (199, 4200, 4, 1),
-    (200, 4200, 4, 0),
+    (129, 4200, 4, 1),      # 129 to 180 units past 4096 rows: parts with records
+    (180, 4200, 8, 1),
+    (181, 4200, 4, 0),
     (256, 12000, 4, 0),
-    (256, 13000, 4, 1),     # 200 to 256 past 12288 rows: parts
-    (256, 13000, 8, 0),     # ... past 16384 for more heads
-    (256, 17000, 8, 1),
+    (256, 13000, 4, 1),     # 181 to 256 past 12288 rows
+    (256, 13000, 8, 0),     # ... of up to four heads
     (257, 1000, 4, 0),      # 257 to 383 of five or six splits: records
     (257, 1300, 4, 1),
     (383, 1300, 4, 1),
