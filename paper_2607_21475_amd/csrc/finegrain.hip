@@ -294,13 +294,18 @@ size_t block_contrib_lds(int64_t nblocks, int gb, int waves) {
   return (size_t)(waves * nblocks + 16 + gb * kHeadDim) * sizeof(float);
 }
 
-// Waves per unit: eight, four of 257 to 512 units, at least two tiles each and bins of at most 64 KB
-// together.  More units fill the chip with a wave each; there the waves' bins and their sum only cost.
-// Units of 1540 rows, G = 4, 2048 blocks, us by 1 / 2 / 4 / 8 waves: 256 units 80 / 46 / 42 / 40, 300 84 / 57 / 62
-// / 65, 512 86 / 82 / 76 / 81, 600 93 / 105 / 99 / 108, 1000 144 / 144 / 142 / 154; 600 units, 8192 blocks
-// 110 / 146.
+// Waves per unit: eight up to 256 units, four up to 512 and, of long units, 1024, else enough for 2048 in the
+// launch; at least two tiles each, and bins of at most 64 KB together.  More units fill the chip with a
+// wave each, and past 512 units so do those with many bins, which fewer and fewer work-groups find room
+// for.  G = 4, us by 1 / 2 / 4 / 8 waves; equal units of 1540 rows, 2048 blocks: 256 units 80 / 46 / 42 / 40, 300
+// 84 / 57 / 62 / 65, 512 86 / 82 / 76 / 81, 600 93 / 105 / 99 / 108, 1000 144 / 144 / 142 / 154; ragged units of up
+// to 1540 rows, 96 blocks: 600 80 / 68 / 58 / 63, 1000 102 / 97 / 93 / 96; 600 equal ones of 1540 rows with
+// 8192 blocks 110 / 146.
 int block_contrib_waves(const BlocksLaunch &L) {
-  int64_t w = L.U <= 256 ? kBlockWaves : L.U <= 512 ? kBlockWaves / 2 : 1;
+  const bool many = L.U > 512, bins = L.nblocks <= 4096;
+  int64_t w = L.U <= 256 ? kBlockWaves : kBlockWaves / 2;
+  if (many && (L.U > 1024 || !bins)) w = 1;
+  else if (many && L.max_rows < 512) w = 2048 / L.U;
   w = w < (L.max_rows + 31) / 32 ? w : (L.max_rows + 31) / 32;
   w = w < 16384 / L.nblocks ? w : 16384 / L.nblocks;
   return (int)(w < 1 ? 1 : w);

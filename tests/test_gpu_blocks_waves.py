@@ -17,16 +17,19 @@ pytestmark = pytest.mark.gpu
     ([3000, 40], 1, 4096, 64),        # ... for four
     ([900, 700], 12, 64, 64),         # two head blocks
     ([700] * 3, 8, 1, 1 << 30),       # one block of everything
-    ([100 + u % 60 for u in range(700)], 2, 64, 64),    # a wave per unit
+    ([100 + u % 60 for u in range(700)], 2, 64, 64),    # two waves per unit
     ([60 + u % 30 for u in range(2100)], 4, 64, 64),
     ([100 + u % 90 for u in range(256)], 3, 64, 64),    # six waves per unit, the most of so short ones
     ([100 + u % 90 for u in range(257)], 3, 64, 64),    # four from here
     ([100 + u % 90 for u in range(512)], 5, 2048, 1),   # ... to here
     ([100 + u % 90 for u in range(513)], 5, 8192, 1),   # a wave per unit, the most blocks
-    ([20 + u % 30 for u in range(520)], 1, 16, 4),
-    ([20 + u % 30 for u in range(520)], 3, 16, 4),
-    ([20 + u % 30 for u in range(520)], 6, 16, 4),
-    ([20 + u % 30 for u in range(520)], 8, 16, 4),
+    ([512, 130] + [40] * 1022, 4, 4096, 1),             # four of up to 1024 long units
+    ([511, 130] + [40] * 600, 7, 64, 16),               # three
+    ([512, 130] + [40] * 700, 2, 4097, 1),              # a wave per unit
+    ([20 + u % 30 for u in range(1030)], 1, 16, 4),
+    ([20 + u % 30 for u in range(1030)], 3, 16, 4),
+    ([20 + u % 30 for u in range(1030)], 6, 16, 4),
+    ([20 + u % 30 for u in range(1030)], 8, 16, 4),
 ])
 def test_block_contributions_over_waves(sizes, G, nb, block_rows):
     print("block contributions over waves: %d units, longest %d, G=%d, %d blocks" % (len(sizes), max(sizes), G, nb), flush=True)
