@@ -1200,8 +1200,10 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
 //    (Two waves per unit and a copy, at 2048 tokens: 64 units, 5%: gathered 18, copied 17.)
 //  * Few rows of 256 units and more are gathered whole (the gathers of some overlap the latency-bound
 //    selection of others), up to three shares (below): 767 units of 16384 tokens, 10%: 290, copied 323, shared
-//    303; 512 of 20000: 273, 283 and 279.  Streamed units of more than 128 tokens for every unit of
-//    the launch gain more from the copy: 300 of 65536, 10%, top-k: 721 and 617; but 512 of 33000: 439 and 445.
+//    303; 512 of 20000: 273, 283 and 279.  Streamed units of more than 128 tokens for every unit of launches
+//    of up to 512 gain more from the copy: 300 of 65536, 10%, top-k: 721 and 617; but 512 of 33000: 439 and
+//    445, and 601 of 131072: 1841, shared 1810, ragged 1149, copied 1170, shared 1050.  (1024 and
+//    more equal units of 131072 lose 3% to the share, 2973 and 3063, where ragged ones gain 7%, 1846 and 1722.)
 //  * More rows: the copy launch wherever the register kernel selects, up to 512 units that are staged in
 //    LDS and 320 that are streamed (25%: 400 units of 16384 tokens, copied 361, shared 371, and ragged 226
 //    and 218; 600: 542 and 542; 300 of 16385: 317 and 326; 512: 484 and 480, and ragged 273 and 265); else a
@@ -1217,7 +1219,7 @@ int32_t evict_gather_rows(const EvictLaunch &L) {
     return few && !mid && capacity <= most ? (int32_t)capacity : 0;
   }
   const bool streamed = n > kEvictStageMax;
-  if (few ? streamed && n > 128 * U : n <= kRegRowsMax || U <= (streamed ? 320 : 512)) return 0;
+  if (few ? streamed && n > 128 * U && U <= 512 : n <= kRegRowsMax || U <= (streamed ? 320 : 512)) return 0;
   const int64_t share = n / 16 / kCopyRows * kCopyRows;
   const int64_t first = share < kGatherMinRows ? kGatherMinRows : share > kGatherMaxRows ? kGatherMaxRows : share;
   return (int32_t)(capacity <= (few ? 3 : 2) * first ? capacity : first);

@@ -37,6 +37,9 @@ def _launches(names, call):
     (330, 16400, 0.10, 0, 0),   # streamed units past those of the segment kernels
     (330, 16400, 0.10, 1, 0),
     (300, 16400, 0.25, 2, 1),
+    (512, 65600, 0.10, 2, 1),   # long units, few rows: copied up to 512 units
+    (513, 65700, 0.10, 2, 0),   # gathered whole
+    (513, 131072, 0.10, 2, 1),  # ... up to three shares
 ])
 def test_evict_gather_launches(units, n, budget, design, copies):
     _say("evict launches units=%d n=%d budget=%s design=%d" % (units, n, budget, design))
