@@ -1202,7 +1202,7 @@ __global__ __launch_bounds__(kCopyThreads) void evict_copy_kernel(EvictLaunch L)
 //    selection of others), up to three shares (below): 767 units of 16384 tokens, 10%: 290, copied 323, shared
 //    303; 512 of 20000: 273, 283 and 279.  Streamed units of more than 128 tokens for every unit of launches
 //    of up to 512 gain more from the copy: 300 of 65536, 10%, top-k: 721 and 617; but 512 of 33000: 439 and
-//    445, and 601 of 131072: 1841, shared 1810, ragged 1149, copied 1170, shared 1050.  (1024 and
+//    445, and 601 of 131072: copied 1841, shared 1810, ragged ones 1170 and 1050.  (1024 and
 //    more equal units of 131072 lose 3% to the share, 2973 and 3063, where ragged ones gain 7%, 1846 and 1722.)
 //  * More rows: the copy launch wherever the register kernel selects, up to 512 units that are staged in
 //    LDS and 320 that are streamed (25%: 400 units of 16384 tokens, copied 361, shared 371, and ragged 226
